@@ -12,6 +12,7 @@ the output of a ReLU).
 import math
 
 import torch
+import torch.nn.functional as F
 
 from paper_1907_02129_amd import binding as icv
 from paper_1907_02129_amd.workloads import ConvShape
@@ -162,7 +163,7 @@ def prepare(c, seed):
         t = torch.bfloat16 if s.dtype == "bf16" else torch.float32
         x, w = x.to(t), (w / red).to(t)
     buf = icv.prepare(s, w, plan=icv.PLAN_PER_IMAGE if c["per_image"] else 0)
-    st = {"x": x, "buf": buf, "rebuild": c["rebuild"], "ep": None}
+    st = {"x": x, "w": w, "buf": buf, "rebuild": c["rebuild"], "ep": None}
     if c["fused"]:
         if s.dtype == "u8i8":
             st["bias"] = (torch.randn(s.K, generator=g, device=dev) * 500).round_().to(torch.int32)
@@ -186,3 +187,25 @@ def run(st):
         return icv.run(buf, st["x"])
     icv.conv2d_nhwc_fused(buf.p, st["x"], buf.packed, buf.indirection, buf.zero_row, st["ep"], st["out"])
     return st["out"]
+
+
+def exact(c, seed):
+    """The same convolution as one matrix product per kernel element in 64 bits.  Integers below 2^53 are exact there;
+    the requantisation of a uint8 output is defined in single precision and is done in it."""
+    st = prepare(c, seed)
+    x, w = st["x"].double(), st["w"].double()
+    zp = float(c["zero_point"]) if c["dtype"] == "u8i8" else 0.0
+    (Hout, Wout), p, d, t = _out(c), c["pad"], c["dilation"], c["stride"]
+    x = F.pad(x - zp, (0, 0, p, p, p, p))
+    y = torch.zeros((c["N"] * Hout * Wout, c["K"]), dtype=torch.float64, device=x.device)
+    for ky in range(c["R"]):
+        for kx in range(c["S"]):
+            rows = x[:, ky * d: ky * d + (Hout - 1) * t + 1: t, kx * d: kx * d + (Wout - 1) * t + 1: t]
+            y.addmm_(rows.reshape(-1, c["C"]), w[:, ky, kx].t())
+    y = y.view(c["N"], Hout, Wout, c["K"])
+    if st["ep"] is not None:
+        y = (y + st["bias"].double()).relu_()
+        if c["dtype"] == "u8i8":
+            return (y.float() * st["ep"].out_scale).round_().clamp_(0, 255).to(torch.uint8)
+        return y
+    return y.to(torch.int32) if c["dtype"] == "u8i8" else y
