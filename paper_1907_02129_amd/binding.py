@@ -309,7 +309,7 @@ def stored_for_tensor_cores(shape):
     to a multiple of 32 (64-byte rows).  fp32 tensors: counts are rounded up to a multiple of 16 (64-byte rows).  The
     padding channels of input and filter hold zeros and `c_logical` keeps the real count (FLOPs are counted on it).
     Shapes that need no padding are returned as they are; the unpadded shape is always valid too and runs on the
-    vector-ALU kernel."""
+    tensor-core kernel for rows of any length."""
     C = shape.C
     if shape.dtype == "f32":
         Cs = -(-C // 16) * 16

@@ -1,5 +1,4 @@
-// Vector-ALU indirect GEMM: serves fp32 and every shape the tensor-core kernels do not take (C not a
-// multiple of the MFMA k-granule, unaligned pixel strides, zero points other than 128).
+// Vector-ALU indirect GEMM: any shape, any type, on request (ICV_PLAN_VECTOR_ALU).
 //
 // It is Listing 3 with one output element per thread: for each kernel element load the row pointer from
 // the indirection buffer (entry = byte offset from the input base; < 0 -> the zero row), take the C-long dot product with the filter row,

@@ -30,6 +30,7 @@ static int64_t out_extent(int64_t in, int64_t lo, int64_t hi, int64_t dil, int64
 static size_t packed_filter_base_bytes(const icv_conv_params* p, const Geometry& g)
 {
     if (g.kind == PLAN_MFMA_LOWC) return (size_t)g.n_tiles * g.NR * g.KCB;
+    if (g.kind == PLAN_MFMA_ANY) return (size_t)any_packed_bytes(g, p->C * g.elem_bytes);
     return (size_t)g.n_tiles * g.NR * g.T * p->C * g.elem_bytes;
 }
 
@@ -62,7 +63,18 @@ int64_t tile_span_bound(const icv_conv_params* p, int64_t Hout, int64_t Wout, in
     return walk + (int64_t)(p->R - 1) * p->DY * Win + (int64_t)(p->S - 1) * p->DX + 1 + (lo > 0 ? lo : 0) + (hi > 0 ? hi : 0);
 }
 
+// 1x1, stride 1, no padding: the input tensor is the matrix
+static bool is_plain_gemm(const icv_conv_params* p)
+{
+    return p->R == 1 && p->S == 1 && p->SY == 1 && p->SX == 1 && p->PT == 0 && p->PL == 0 && p->PB == 0 && p->PR == 0;
+}
+
 static const char* kGenericNames[3] = {"generic_f32", "generic_bf16", "generic_u8i8"};
+static const char* kAnyNames[3][4] = {
+    {"generic_f32_mfma_128x128", "generic_f32_mfma_128x64", "generic_f32_mfma_64x64", "generic_f32_mfma_128x32"},
+    {"generic_bf16_mfma_128x128", "generic_bf16_mfma_128x64", "generic_bf16_mfma_64x64", "generic_bf16_mfma_128x32"},
+    {"generic_i8_mfma_128x128", "generic_i8_mfma_128x64", "generic_i8_mfma_64x64", "generic_i8_mfma_128x32"},
+};
 static const char* kLowcNames[2] = {"mfma_bf16_lowc_64x64", "mfma_i8_lowc_64x64"};
 // filter in registers: [dtype][column blocks per workgroup 1, 2, 4][row blocks per wavefront and pass 1, 2]
 static const char* kFregNames[3][3][2] = {
@@ -329,11 +341,23 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         g->name = (patch_rows ? kPatchNames : kMfmaNames)[name_row][variant];
         // Section 3.2, closing paragraph: a 1x1 stride-1 convolution needs no im2col, the plain GEMM primitive has
         // the edge there and switching between the two primitives by convolution parameters is advised.  Its A matrix is the input tensor; the indirection buffer is built but not read.
-        if (T == 1 && p->SY == 1 && p->SX == 1 && p->PT == 0 && p->PL == 0 && p->PB == 0 && p->PR == 0 &&
-            plan_staging != 1) {
+        if (is_plain_gemm(p) && plan_staging != 1) {
             g->gemm_on_input = 1;
             g->name = kGemmNames[name_row][variant];
         }
+    } else if (plan_kernel != 1 && T * row_bytes < (1ll << 31)) {
+        // rows of any other length or alignment
+        g->kind = PLAN_MFMA_ANY;
+        g->variant = choose_any_tile(M, p->K, (int32_t)row_bytes, plan_per_image);
+        g->MR = kAnyTiles[g->variant].MR;
+        g->NR = kAnyTiles[g->variant].NR;
+        g->KCB = 0;
+        g->ring = 0;
+        g->blocks_per_cu = 0;
+        g->stages_per_tap = 1;
+        g->taps_per_stage = 1;
+        g->n_stages = g->T;
+        g->name = kAnyNames[p->dtype][g->variant];
     } else {
         g->kind = PLAN_GENERIC;
         g->variant = -1;
@@ -543,6 +567,10 @@ static int conv_common(const icv_conv_params* p, Geometry g, const void* a, cons
         return launch_igemm_mfma(p, g, a, packed, ind, zero_row, out,
                                  a_direct ? A_DENSE_WORKSPACE : (g.gemm_on_input ? A_DENSE_INPUT : A_GATHERED), s);
     if (g.kind == PLAN_MFMA_LOWC) return launch_igemm_lowc(p, g, a, packed, ind, zero_row, out, a_direct, s);
+    if (g.kind == PLAN_MFMA_ANY)
+        return launch_igemm_any(p, g, a, packed, ind, zero_row, out,
+                                a_direct ? A_DENSE_WORKSPACE
+                                         : (is_plain_gemm(p) && (p->plan & 7) != ICV_PLAN_GATHER ? A_DENSE_INPUT : A_GATHERED), s);
     return launch_igemm_generic(p, g, a, packed, ind, zero_row, out, a_direct, s);
 }
 

@@ -1,0 +1,72 @@
+// Host side of the any-channel-count kernel: which tile, and the launch.
+#include "icv_igemm_any_kernel.h"
+
+namespace icv {
+
+const TileVariant kAnyTiles[] = {
+    {128, 128, 1, 4, "128x128"},
+    {128, 64, 2, 2, "128x64"},
+    {64, 64, 2, 2, "64x64"},
+    {128, 32, 4, 1, "128x32"},
+};
+
+int choose_any_tile(int64_t M, int32_t K, int32_t row_bytes, bool any_batch)
+{
+    if (row_bytes < 16) return 2;      // rows shorter than a piece: built for this tile only
+    if (K <= 32) return 3;
+    const int wide = K <= 64 ? 1 : 0;
+    // 64 x 64 when the wider tile leaves most of the chip with a single workgroup or none: two and more per compute
+    // unit are what hides this kernel's latencies.  A batch-independent buffer's layout must not depend on N.
+    const int64_t tiles = ((M + 127) / 128) * ((K + kAnyTiles[wide].NR - 1) / kAnyTiles[wide].NR);
+    return any_batch || tiles >= 512 ? wide : 2;
+}
+
+int64_t any_packed_bytes(const Geometry& g, int32_t row_bytes)
+{
+    const int64_t P = (row_bytes + 15) / 16;
+    return g.n_tiles * (g.NR / 32) * ((g.T * P + 1) / 2) * 1024;
+}
+
+int launch_igemm_any(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
+                     const int32_t* ind, const void* zero_row, void* out, int a_mode, hipStream_t s)
+{
+    AnyArgs a{};      // every field starts at zero; the ones this call uses are set below
+    a.a = (const uint8_t*)input;
+    a.zero_row = (const uint8_t*)zero_row;
+    a.w = (const uint8_t*)packed;
+    a.ind = a_mode == A_GATHERED ? ind : nullptr;
+    a.out = out;
+    a.row_bytes = p->C * g.elem_bytes;
+    a.a_row_stride = a_mode == A_DENSE_WORKSPACE ? (int64_t)g.T * a.row_bytes : (int64_t)g.in_stride * g.elem_bytes;
+    a.a_rows = a_mode == A_DENSE_WORKSPACE ? g.m_tiles * g.MR : g.M;
+    a.image_bytes = a_mode == A_GATHERED ? g.image_bytes : 0;
+    a.img_tiles = (uint32_t)g.img_tiles;
+    a.img_rows = (uint32_t)g.img_rows;
+    const int64_t tiles = g.m_tiles * g.n_tiles;
+    if (tiles >= (1ll << 31) - 8) return ICV_ERR_UNSUPPORTED;
+    a.total_tiles = (uint32_t)tiles;
+    a.tiles_per_xcd = (uint32_t)((tiles + 7) / 8);
+    a.n_tiles = (uint32_t)g.n_tiles;
+    a.by_n_tiles = make_fast_div(a.n_tiles);
+    a.by_img_tiles = make_fast_div(a.img_tiles);
+    a.K = p->K; a.T = g.T; a.out_stride = g.out_stride;
+    a.P = (a.row_bytes + 15) / 16;
+    a.n_pieces = g.T * a.P;
+    a.step_taps = 8 / a.P;
+    a.step_pieces = 8 % a.P;
+    a.n_steps = (a.n_pieces + 1) / 2;
+    a.n_stages = (a.n_steps + 3) / 4;
+    const int tail = a.row_bytes % 16 == 0 ? ROWS_WHOLE : (a.row_bytes > 16 ? ROWS_TAIL : ROWS_SHORT);
+    a.tail_shift = tail == ROWS_TAIL ? 16 - a.row_bytes % 16 : 0;
+    a.ep = g.ep;
+    const TileVariant& tv = kAnyTiles[g.variant];
+    if (tv.MR != g.MR || tv.NR != g.NR) return ICV_ERR_UNSUPPORTED;
+    switch (p->dtype) {
+    case ICV_BF16: return launch_any_bf16(a, g.variant, tail, !g.ep_plain, s);
+    case ICV_U8I8: return launch_any_u8(a, g.variant, tail, !g.ep_plain, s);
+    case ICV_F32: return launch_any_f32(a, g.variant, tail, !g.ep_plain, s);
+    }
+    return ICV_ERR_UNSUPPORTED;
+}
+
+}  // namespace icv

@@ -10,10 +10,11 @@ namespace icv {
 // Which inner kernel serves a problem.
 enum PlanKind : int32_t {
     PLAN_INVALID = 0,
-    PLAN_GENERIC = 1,   // vector-ALU kernel, any C, any dtype
+    PLAN_GENERIC = 1,   // vector-ALU kernel, any C, any dtype (on request)
     PLAN_MFMA = 2,      // tensor-core indirect GEMM, C a multiple of the k-granule
     PLAN_MFMA_LOWC = 3, // tensor-core indirect GEMM for pixel rows of 8, 16 or 32 bytes (first-layer convolutions)
-    PLAN_MFMA_FREG = 4  // tensor-core indirect GEMM with the filter in registers and the input window in an LDS ring
+    PLAN_MFMA_FREG = 4, // tensor-core indirect GEMM with the filter in registers and the input window in an LDS ring
+    PLAN_MFMA_ANY = 5   // tensor-core indirect GEMM for rows of any length and alignment
 };
 
 // Output stage of icv_conv2d_nhwc_fused, as the kernels see it (icv_epilogue with the bias pointer typed by use).
@@ -144,6 +145,11 @@ size_t freg_lds_bytes(int T, int KS, int PBK, int ring_rows);
 size_t patch_lds_bytes(int NR, int KCB, int ring, int cap_units, int ent_copies, int nbuf);
 int launch_igemm_lowc(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                       const int32_t* ind, const void* zero_row, void* out, bool a_direct, hipStream_t s);
+// the any-channel-count kernel: tile for a problem (any_batch: independent of the batch size), bytes of its filter
+int choose_any_tile(int64_t M, int32_t K, int32_t row_bytes, bool any_batch);
+int64_t any_packed_bytes(const Geometry& g, int32_t row_bytes);
+int launch_igemm_any(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
+                     const int32_t* ind, const void* zero_row, void* out, int a_mode, hipStream_t s);
 int launch_igemm_generic(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                          const int32_t* ind, const void* zero_row, void* out, bool a_direct, hipStream_t s);
 
@@ -159,5 +165,6 @@ struct TileVariant {
 // pipeline stage of the pixel-range kernel.
 extern const TileVariant kTileVariants[];
 extern const int kNumTileVariants;
+extern const TileVariant kAnyTiles[];      // tiles of the any-channel-count kernel
 
 }  // namespace icv

@@ -80,22 +80,33 @@ __global__ void k_pack_filter_lowc(const uint8_t* src, uint8_t* dst, int K, int 
     *(uint2*)(dst + row * (int64_t)KP + b) = v;
 }
 
-// Filter-in-registers plan: [block of 32 output channels][fragment = tap * KS + step][lane][16 bytes], the operand
-// layout of the 32x32 MFMAs -- lane l holds bytes 32*step + 16*(l >> 5) .. +16 of kernel element `tap` of channel
-// 32*block + (l & 31) -- so that a wavefront loads a fragment with one coalesced 1 KB read.  Channels past K are zero.
-__global__ void k_pack_filter_frag(const uint8_t* src, uint8_t* dst, int K, int T, int KS, int64_t total_vec)
+// Filter-in-registers and any-channel-count plans: [block of 32 output channels][MFMA step][lane][16 bytes], the
+// operand layout of the 32x32 MFMAs, so that a wavefront loads a fragment with one coalesced 1 KB read.  A kernel
+// element's channels are P pieces of 16 bytes, the last one padded with zeros; the T*P pieces follow each other and a
+// step takes two of them: lane l holds piece 2 * step + (l >> 5) of output channel 32 * block + (l & 31).  Channels
+// past K and pieces past the last are zero.
+__global__ void k_pack_filter_frag(const uint8_t* src, uint8_t* dst, int K, int T, int row_bytes, int64_t total_vec)
 {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= total_vec) return;
     const int lane = (int)(v & 63);
     const int64_t fi = v >> 6;
-    const int f = (int)(fi % (T * KS));
-    const int cb = (int)(fi / (T * KS));
-    const int tap = f / KS, ks = f - tap * KS;
-    const int oc = cb * 32 + (lane & 31);
-    uint4 val = make_uint4(0, 0, 0, 0);
-    if (oc < K) val = *(const uint4*)(src + ((int64_t)oc * T + tap) * (KS * 32) + ks * 32 + (lane >> 5) * 16);
-    *(uint4*)(dst + v * 16) = val;
+    const int P = (row_bytes + 15) / 16, steps = (T * P + 1) / 2;
+    const int f = (int)(fi % steps);
+    const int64_t oc = fi / steps * 32 + (lane & 31);
+    const int j = 2 * f + (lane >> 5), tap = j / P, at = (j - tap * P) * 16;
+    uint32_t val[4] = {0, 0, 0, 0};
+    if (oc < K && tap < T) {
+        const uint8_t* s = src + (oc * T + tap) * row_bytes + at;
+        if (at + 16 <= row_bytes) {
+            __builtin_memcpy(val, s, 16);
+        } else {
+#pragma unroll
+            for (int b = 0; b < 15; b++)
+                if (at + b < row_bytes) val[b >> 2] |= (uint32_t)s[b] << (8 * (b & 3));
+        }
+    }
+    *(uint4*)(dst + v * 16) = make_uint4(val[0], val[1], val[2], val[3]);
 }
 
 // uint8 tensor-core plans: sums[k] = sum over the R*S*C filter elements of output channel k (the zero-point term of
@@ -120,12 +131,10 @@ int launch_pack_filter(const icv_conv_params* p, const Geometry& g, const void* 
                            (int32_t*)((uint8_t*)packed + g.wsum_offset), p->K, (int64_t)g.T * p->C);
         ICV_HIP_CHECK(hipGetLastError());
     }
-    if (g.kind == PLAN_MFMA_FREG) {
-        const int KS = g.KCB / 32;
-        const int64_t col_blocks = g.n_tiles * (g.NR / 32);
-        const int64_t total = col_blocks * g.T * KS * 64;
+    if (g.kind == PLAN_MFMA_FREG || g.kind == PLAN_MFMA_ANY) {
+        const int64_t P = (CB + 15) / 16, total = g.n_tiles * (g.NR / 32) * ((g.T * P + 1) / 2) * 64;
         hipLaunchKernelGGL(k_pack_filter_frag, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
-                           (const uint8_t*)filt, (uint8_t*)packed, p->K, g.T, KS, total);
+                           (const uint8_t*)filt, (uint8_t*)packed, p->K, g.T, (int)CB, total);
         ICV_HIP_CHECK(hipGetLastError());
         return ICV_OK;
     }

@@ -1,0 +1,69 @@
+"""Rows of any length and alignment on the tensor cores: every tile, row lengths around the 16-byte piece, ragged
+pixel and channel counts, dense and gathered rows, the patch-matrix product, and what a row's neighbours hold.
+
+Tolerances as in test_gpu_parity.py: exact for u8i8, the fp32 accumulation bound (any order) for the others."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1907_02129_amd import binding as icv
+from paper_1907_02129_amd.workloads import ConvShape, make_tensors
+from test_gpu_parity import check_against_oracle, run_im2col, run_indirect
+
+pytestmark = pytest.mark.gpu
+
+
+def _shapes():
+    out = []
+    # channels: bytes per row below, at and above whole 16-byte pieces; K: one, two and more column blocks, ragged
+    for i, (dtype, C, K) in enumerate([("bf16", 5, 33), ("bf16", 40, 24), ("bf16", 9, 65), ("bf16", 24, 130), ("bf16", 48, 192),
+                                       ("bf16", 37, 8), ("bf16", 100, 64), ("u8i8", 7, 40), ("u8i8", 15, 20), ("u8i8", 17, 70),
+                                       ("u8i8", 48, 129), ("u8i8", 96, 32), ("f32", 1, 9), ("f32", 3, 64), ("f32", 5, 31),
+                                       ("f32", 8, 66), ("f32", 33, 140)]):
+        zp = (0, 128, 77)[i % 3] if dtype == "u8i8" else 0
+        out.append(ConvShape(f"any_{dtype}_c{C}_k{K}", 2, 13, 11, C, K, 3, 3, SY=1 + i % 2, PT=1, PL=1, PB=1, PR=1,
+                             dtype=dtype, zero_point=zp, seed=600 + i))
+    # enough row tiles for the 128-row tiles (K > 32: at least 512 workgroups of 128 rows)
+    out.append(ConvShape("any_wide_128x128", 3, 150, 147, 12, 70, 1, 2, seed=630))
+    out.append(ConvShape("any_wide_128x64", 3, 149, 148, 18, 64, 2, 1, dtype="u8i8", zero_point=5, seed=631))
+    # 1x1: the input itself is the matrix
+    out.append(ConvShape("any_1x1_bf16", 3, 9, 7, 40, 72, 1, 1, seed=632))
+    out.append(ConvShape("any_1x1_u8", 2, 17, 5, 33, 48, 1, 1, dtype="u8i8", zero_point=200, seed=633))
+    out.append(ConvShape("any_one_pixel", 1, 1, 1, 24, 8, 1, 1, seed=634))
+    return out
+
+
+@pytest.mark.parametrize("plan", [0, icv.PLAN_PER_IMAGE, icv.PLAN_GATHER], ids=["auto", "per_image", "gather"])
+@pytest.mark.parametrize("s", _shapes(), ids=lambda s: s.name)
+def test_any_channel_count_matches_oracle(s, plan):
+    name = icv.plan_name(icv.make_params(s, plan=plan))
+    print("conv", s.name, name, flush=True)
+    assert name.startswith("generic_")
+    x, w = make_tensors(s)
+    buf, xd = run_indirect(s, x, w, plan=plan)
+    check_against_oracle(s, buf.output.cpu().numpy(), x, w)
+    out2, _ = run_im2col(s, buf, xd)
+    check_against_oracle(s, out2.cpu().numpy(), x, w)
+
+
+@pytest.mark.parametrize("dtype,C", [("bf16", 20), ("f32", 7), ("bf16", 5)])
+def test_a_row_never_sees_its_neighbours(dtype, C):
+    """One pixel full of infinities and NaN, in a tensor whose pixels are further apart than C with NaN in between:
+    exactly the outputs whose window holds that pixel are affected."""
+    s = ConvShape("any_nan", 1, 9, 10, C, 36, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype=dtype, seed=640)
+    x, w = make_tensors(s)
+    buf, xd = run_indirect(s, x, w)
+    clean = buf.output.clone()
+    stride = C + 3
+    wide = torch.full((1, 9, 10, stride), float("nan"), dtype=xd.dtype, device="cuda:0")
+    wide[..., :C] = xd
+    wide[0, 4, 5, :C] = float("inf")
+    wide[0, 4, 5, 0] = float("nan")
+    b2 = icv.prepare(s, icv.to_device(w), in_pixel_stride=stride)
+    icv.run(b2, wide.contiguous())
+    torch.cuda.synchronize()
+    hit = np.zeros((9, 10), bool)
+    hit[3:6, 4:7] = True
+    got = b2.output[0].cpu().numpy()
+    assert np.isnan(got[hit]).all()
+    assert np.array_equal(got[~hit], clean[0].cpu().numpy()[~hit])
