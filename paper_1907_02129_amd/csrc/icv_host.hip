@@ -75,7 +75,10 @@ static const char* kAnyNames[3][4] = {
     {"generic_bf16_mfma_128x128", "generic_bf16_mfma_128x64", "generic_bf16_mfma_64x64", "generic_bf16_mfma_128x32"},
     {"generic_i8_mfma_128x128", "generic_i8_mfma_128x64", "generic_i8_mfma_64x64", "generic_i8_mfma_128x32"},
 };
-static const char* kLowcNames[2] = {"mfma_bf16_lowc_64x64", "mfma_i8_lowc_64x64"};
+static const char* kLowcNames[2][3] = {
+    {"", "mfma_bf16_lowc_64x64", "mfma_i8_lowc_64x64"},
+    {"generic_f32_lowc_64x64", "generic_bf16_lowc_64x64", "generic_i8_lowc_64x64"},     // rows of any alignment
+};
 // filter in registers: [dtype][column blocks per workgroup 1, 2, 4][row blocks per wavefront and pass 1, 2]
 static const char* kFregNames[3][3][2] = {
     {{"mfma_f32_freg_w1m1", "mfma_f32_freg_w1m2"}, {"mfma_f32_freg_w2m1", "mfma_f32_freg_w2m2"},
@@ -283,9 +286,9 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         return ICV_ERR_UNSUPPORTED;
     }
     // very short rows (first-layer convolutions): the whole reduction of a tile is gathered at once
-    const bool lowc_ok = p->dtype != ICV_F32 && plan_kernel == 0 &&
-                         (row_bytes == 8 || row_bytes == 16 || row_bytes == 32) && stride_bytes % row_bytes == 0 &&
-                         T * row_bytes <= 608;
+    const bool lowc_words = p->dtype != ICV_F32 && (row_bytes == 8 || row_bytes == 16 || row_bytes == 32);
+    const bool lowc_ok = plan_kernel == 0 && lowc_shape_supported(p->dtype, row_bytes) &&
+                         (!lowc_words || stride_bytes % row_bytes == 0) && T * row_bytes <= 608;
     g->freg_wn = freg_wn; g->freg_mb = freg_mb; g->freg_ring = freg_ring;
     if (freg_mb) {
         g->kind = PLAN_MFMA_FREG;
@@ -311,7 +314,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         g->stages_per_tap = 1;
         g->taps_per_stage = g->T;
         g->n_stages = 1;
-        g->name = kLowcNames[p->dtype == ICV_U8I8 ? 1 : 0];
+        g->name = kLowcNames[lowc_words ? 0 : 1][p->dtype];
         // compact entries (16-bit pixel numbers inside the tile's range) when every tile's range is short enough;
         // plan "rows gathered per kernel element" keeps the int32 offsets, for comparison
         const int64_t span = tile_span_bound(p, Hout, Wout, 64);

@@ -41,17 +41,63 @@ struct LowcArgs {
     EpilogueArgs ep;
 };
 
-// register type of one gathered piece (native vectors: arrays of them are kept in registers)
+// One gathered piece of U bytes in registers.  Rows of 8, 16 and 32 bytes lie at multiples of 8 and move as native
+// vectors (arrays of them are kept in registers); shorter rows and the 12-byte ones (three fp32 channels) may lie at any
+// address and are moved by 32-, 16- and 8-bit loads, which is also what their places in the LDS row are aligned to.
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 template <int U>
-struct Piece;
+struct Piece { using type = uint32_t; };                      // 1, 2, 3, 4 bytes
+template <>
+struct Piece<6> { using type = u32x2_t; };
 template <>
 struct Piece<8> { using type = u32x2_t; };
+template <>
+struct Piece<12> { using type = u32x3_t; };
 template <>
 struct Piece<16> { using type = u32x4_t; };
 template <>
 struct Piece<32> { using type = u32x4_t; };   // moved as two 16-byte halves
+
+template <typename T>
+__device__ inline uint32_t load_part(const uint8_t* p)        // one element of T from an address T need not be aligned to
+{
+    T v;
+    __builtin_memcpy(&v, p, sizeof(T));
+    return (uint32_t)v;
+}
+
+template <int U>
+__device__ inline typename Piece<U>::type load_piece(const uint8_t* p)
+{
+    using piece_t = typename Piece<U>::type;
+    if constexpr (U == 1) return load_part<uint8_t>(p);
+    else if constexpr (U == 2) return load_part<uint16_t>(p);
+    else if constexpr (U == 3) return load_part<uint16_t>(p) | load_part<uint8_t>(p + 2) << 16;
+    else if constexpr (U == 4) return load_part<uint32_t>(p);
+    else if constexpr (U == 6) return piece_t{load_part<uint32_t>(p), load_part<uint16_t>(p + 4)};
+    else if constexpr (U == 12) { piece_t v; __builtin_memcpy(&v, p, 12); return v; }
+    else return *(const piece_t*)p;
+}
+
+template <int U>
+__device__ inline void store_piece(uint8_t* d, const typename Piece<U>::type& v)
+{
+    if constexpr (U == 1) {
+        *d = (uint8_t)v;
+    } else if constexpr (U == 2) {
+        *(uint16_t*)d = (uint16_t)v;
+    } else if constexpr (U == 3) {
+        d[0] = (uint8_t)v; d[1] = (uint8_t)(v >> 8); d[2] = (uint8_t)(v >> 16);
+    } else if constexpr (U == 6) {
+        ((uint16_t*)d)[0] = (uint16_t)v.x; ((uint16_t*)d)[1] = (uint16_t)(v.x >> 16); ((uint16_t*)d)[2] = (uint16_t)v.y;
+    } else if constexpr (U == 12) {
+        ((uint32_t*)d)[0] = v.x; ((uint32_t*)d)[1] = v.y; ((uint32_t*)d)[2] = v.z;
+    } else {
+        *(typename Piece<U>::type*)d = v;
+    }
+}
 
 // A team of 4 wavefronts per tile of 64 rows x (32 * col_blocks) columns; its 32 x 32 blocks are dealt out to the
 // wavefronts in turn.  A workgroup is TEAMS such teams that share the filter slice in LDS and each own a gathered
@@ -62,10 +108,11 @@ struct Piece<32> { using type = u32x4_t; };   // moved as two 16-byte halves
 constexpr int kMaxColBlocks = 8;                              // 32-column blocks of a workgroup (256 columns)
 constexpr int kMaxBlocksPerWave = 2 * kMaxColBlocks / 4;      // its 32 x 32 blocks, dealt to four wavefronts
 
-template <bool I8, int U, bool FUSED, int TEAMS>
+template <int DT, int U, bool FUSED, int TEAMS>
 __global__ __launch_bounds__(256 * TEAMS) void k_igemm_lowc(LowcArgs g)
 {
     constexpr int MR = 64;
+    constexpr bool I8 = DT == ICV_U8I8;
     using acc_t = typename std::conditional<I8, i32x16_t, f32x16_t>::type;
     using out_t = typename std::conditional<I8, int32_t, float>::type;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
@@ -91,11 +138,13 @@ __global__ __launch_bounds__(256 * TEAMS) void k_igemm_lowc(LowcArgs g)
     }
     // zero the k padding of the A rows once (those columns are never written by the gather)
     {
-        const int pad_from = g.T * U;             // multiple of 8
-        const int pad8 = (g.KP - pad_from) / 8;
-        for (int v = tid; v < MR * pad8; v += 256) {
-            const int row = v / pad8, c = v - row * pad8;
-            *(uint2*)(ldsA + row * pitch + pad_from + c * 8) = make_uint2(0, 0);
+        using unit_t = typename std::conditional<U % 8 == 0, uint64_t, typename std::conditional<U % 4 == 0, uint32_t,
+                       typename std::conditional<U % 2 == 0, uint16_t, uint8_t>::type>::type>::type;
+        const int pad_from = g.T * U;             // multiple of the unit
+        const int pad = (g.KP - pad_from) / (int)sizeof(unit_t);
+        for (int v = tid; v < MR * pad; v += 256) {
+            const int row = v / pad, c = v - row * pad;
+            *(unit_t*)(ldsA + row * pitch + pad_from + c * (int)sizeof(unit_t)) = 0;
         }
     }
 
@@ -107,7 +156,7 @@ __global__ __launch_bounds__(256 * TEAMS) void k_igemm_lowc(LowcArgs g)
     // Entries of a batch of kernel elements of row tile mt: thread -> row tid % 64, elements tap0, tap0 + 4, ...
     // (the 64 entries of an element are contiguous).  A batch is 16 elements, or 8 of the 32-byte rows.
     constexpr int NB = U == 32 ? 8 : 16;
-    constexpr int NV = U == 32 ? 2 * NB : NB;             // 16-byte (8-byte for U = 8) registers of a batch
+    constexpr int NV = U == 32 ? 2 * NB : NB;             // registers of a batch
     using piece_t = typename Piece<U>::type;
     const int n_taps = g.direct ? 0 : g.T;
     uint8_t* dstrow = ldsA + (tid & 63) * pitch;
@@ -142,7 +191,7 @@ __global__ __launch_bounds__(256 * TEAMS) void k_igemm_lowc(LowcArgs g)
                 v[2 * j] = *(const piece_t*)src;
                 v[2 * j + 1] = *(const piece_t*)(src + 16);
             } else {
-                v[j] = *(const piece_t*)src;
+                v[j] = load_piece<U>(src);
             }
         }
     };
@@ -155,7 +204,7 @@ __global__ __launch_bounds__(256 * TEAMS) void k_igemm_lowc(LowcArgs g)
                     *(piece_t*)(dstrow + tap * 32) = v[2 * j];
                     *(piece_t*)(dstrow + tap * 32 + 16) = v[2 * j + 1];
                 } else {
-                    *(piece_t*)(dstrow + tap * U) = v[j];
+                    store_piece<U>(dstrow + tap * U, v[j]);
                 }
             }
         }
@@ -182,15 +231,8 @@ __global__ __launch_bounds__(256 * TEAMS) void k_igemm_lowc(LowcArgs g)
             for (int ks = 0; ks < ksteps; ks++) {
                 const uint4 av = *(const uint4*)(a_frag + ks * 32);
                 const uint4 bv = *(const uint4*)(b_frag + ks * 32);
-                if constexpr (I8) {
-                    i32x4_t ai = {(int)(av.x ^ 0x80808080u), (int)(av.y ^ 0x80808080u), (int)(av.z ^ 0x80808080u),
-                                  (int)(av.w ^ 0x80808080u)};
-                    i32x4_t bi = {(int)bv.x, (int)bv.y, (int)bv.z, (int)bv.w};
-                    acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(ai, bi, acc, 0, 0, 0);
-                } else {
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av),
-                                                                  __builtin_bit_cast(bf16x8_t, bv), acc, 0, 0, 0);
-                }
+                if constexpr (DT == ICV_F32) acc = mfma32_f32(av, bv, acc);
+                else acc = mfma32<I8>(av, bv, acc);
             }
             const int64_t m_base = img_row0 + (int64_t)t_img * MR + rb * 32 + 4 * lhalf;
             const int32_t col = col0 + cb * 32 + lrow;
@@ -234,7 +276,7 @@ __global__ __launch_bounds__(256 * TEAMS) void k_igemm_lowc(LowcArgs g)
                         v[2 * j] = *(const piece_t*)(base + off);
                         v[2 * j + 1] = *(const piece_t*)(base + off + 16);
                     } else {
-                        v[j] = *(const piece_t*)(base + off);
+                        v[j] = load_piece<U>(base + off);
                     }
                 }
         };
@@ -248,7 +290,7 @@ __global__ __launch_bounds__(256 * TEAMS) void k_igemm_lowc(LowcArgs g)
                         *(piece_t*)d = z ? (piece_t)zfill : v[2 * j];
                         *(piece_t*)(d + 16) = z ? (piece_t)zfill : v[2 * j + 1];
                     } else {
-                        *(piece_t*)d = z ? (piece_t)zfill : v[j];
+                        store_piece<U>(d, z ? (piece_t)zfill : v[j]);
                     }
                 }
         };
@@ -309,6 +351,38 @@ __global__ __launch_bounds__(256 * TEAMS) void k_igemm_lowc(LowcArgs g)
     }
 }
 
+template <int DT, int U, int TEAMS>
+static int launch_lowc(const LowcArgs& a, dim3 grid, size_t lds_bytes, bool plain, hipStream_t s)
+{
+    auto kern = plain ? k_igemm_lowc<DT, U, false, TEAMS> : k_igemm_lowc<DT, U, true, TEAMS>;
+    if (lds_bytes > 64 * 1024) {
+        static bool raised[2][kMaxDevices] = {};         // per instantiation and device
+        const int st = allow_full_lds((const void*)kern, raised[plain ? 0 : 1]);
+        if (st != ICV_OK) return st;
+    }
+    hipLaunchKernelGGL(kern, grid, dim3(256 * TEAMS), lds_bytes, s, a);
+    ICV_HIP_CHECK(hipGetLastError());
+    return ICV_OK;
+}
+
+template <int DT, int U>
+static int launch_lowc_teams(const LowcArgs& a, dim3 grid, int teams, size_t lds_bytes, bool plain, hipStream_t s)
+{
+    if (teams == 4) {
+        if constexpr (U <= 8) return launch_lowc<DT, U, 4>(a, grid, lds_bytes, plain, s);      // wider rows: two at most
+        return ICV_ERR_UNSUPPORTED;
+    }
+    return teams == 2 ? launch_lowc<DT, U, 2>(a, grid, lds_bytes, plain, s) : launch_lowc<DT, U, 1>(a, grid, lds_bytes, plain, s);
+}
+
+// rows the kernel is built for, by type
+bool lowc_shape_supported(int dtype, int64_t row_bytes)
+{
+    if (dtype == ICV_F32) return row_bytes == 4 || row_bytes == 8 || row_bytes == 12;
+    if (row_bytes == 8 || row_bytes == 16 || row_bytes == 32) return true;
+    return dtype == ICV_BF16 ? row_bytes <= 6 : row_bytes <= 4;
+}
+
 int launch_igemm_lowc(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                       const int32_t* ind, const void* zero_row, void* out, bool a_direct, hipStream_t s)
 {
@@ -347,7 +421,6 @@ int launch_igemm_lowc(const icv_conv_params* p, const Geometry& g, const void* i
     a.col_blocks = (kb_total + groups - 1) / groups;
     if (groups > 65535) return ICV_ERR_UNSUPPORTED;
     const int unit = p->C * g.elem_bytes;
-    const bool i8 = p->dtype == ICV_U8I8;
     // Teams per workgroup: the path that gathers a whole tile from compact entries in one batch runs several teams
     // on one filter slice (four for the 8-byte rows, two for the wider ones, whose batches need twice the
     // registers), one workgroup per compute unit; every other path runs single teams, two workgroups per compute unit.
@@ -356,7 +429,7 @@ int launch_igemm_lowc(const icv_conv_params* p, const Geometry& g, const void* i
     int teams = 1;
     if (!a_direct && a.rows && g.T <= batch_taps) {
         const int fit = (int)((kLdsPerCu - b_bytes) / a_bytes);
-        const int want = unit == 8 ? 4 : 2;
+        const int want = unit <= 8 ? 4 : 2;
         teams = fit >= want ? want : (fit >= 2 ? 2 : 1);
     }
     const size_t lds_bytes = b_bytes + teams * a_bytes;
@@ -365,30 +438,27 @@ int launch_igemm_lowc(const icv_conv_params* p, const Geometry& g, const void* i
     if (gx < 1) gx = 1;
     if (gx * teams > g.m_tiles) gx = (g.m_tiles + teams - 1) / teams;
     const dim3 grid((unsigned)gx, (unsigned)groups);
-#define ICV_LOWC_LAUNCH_T(I8, U, TEAMS)                                                                         \
-    do {                                                                                                        \
-        auto kern = g.ep_plain ? k_igemm_lowc<I8, U, false, TEAMS> : k_igemm_lowc<I8, U, true, TEAMS>;          \
-        if (lds_bytes > 64 * 1024) {                                                                            \
-            static bool raised[2][kMaxDevices] = {};         /* per instantiation and device */                \
-            const int st_ = allow_full_lds((const void*)kern, raised[g.ep_plain ? 0 : 1]);                      \
-            if (st_ != ICV_OK) return st_;                                                                      \
-        }                                                                                                       \
-        hipLaunchKernelGGL(kern, grid, dim3(256 * TEAMS), lds_bytes, s, a);                                     \
-    } while (0)
-#define ICV_LOWC_LAUNCH(I8, U)                                                                                  \
-    do {                                                                                                        \
-        if (teams == 4) ICV_LOWC_LAUNCH_T(I8, U, 4);                                                            \
-        else if (teams == 2) ICV_LOWC_LAUNCH_T(I8, U, 2);                                                       \
-        else ICV_LOWC_LAUNCH_T(I8, U, 1);                                                                       \
-    } while (0)
-    if (unit == 8) { if (i8) ICV_LOWC_LAUNCH(true, 8); else ICV_LOWC_LAUNCH(false, 8); }
-    else if (unit == 16) { if (i8) ICV_LOWC_LAUNCH(true, 16); else ICV_LOWC_LAUNCH(false, 16); }
-    else if (unit == 32) { if (i8) ICV_LOWC_LAUNCH(true, 32); else ICV_LOWC_LAUNCH(false, 32); }
-    else return ICV_ERR_UNSUPPORTED;
-#undef ICV_LOWC_LAUNCH
-#undef ICV_LOWC_LAUNCH_T
-    ICV_HIP_CHECK(hipGetLastError());
-    return ICV_OK;
+    switch (p->dtype * 64 + unit) {
+#define ICV_LOWC_CASE(DT, U) case DT * 64 + U: return launch_lowc_teams<DT, U>(a, grid, teams, lds_bytes, g.ep_plain, s);
+    ICV_LOWC_CASE(ICV_BF16, 2)
+    ICV_LOWC_CASE(ICV_BF16, 4)
+    ICV_LOWC_CASE(ICV_BF16, 6)
+    ICV_LOWC_CASE(ICV_BF16, 8)
+    ICV_LOWC_CASE(ICV_BF16, 16)
+    ICV_LOWC_CASE(ICV_BF16, 32)
+    ICV_LOWC_CASE(ICV_U8I8, 1)
+    ICV_LOWC_CASE(ICV_U8I8, 2)
+    ICV_LOWC_CASE(ICV_U8I8, 3)
+    ICV_LOWC_CASE(ICV_U8I8, 4)
+    ICV_LOWC_CASE(ICV_U8I8, 8)
+    ICV_LOWC_CASE(ICV_U8I8, 16)
+    ICV_LOWC_CASE(ICV_U8I8, 32)
+    ICV_LOWC_CASE(ICV_F32, 4)
+    ICV_LOWC_CASE(ICV_F32, 8)
+    ICV_LOWC_CASE(ICV_F32, 12)
+#undef ICV_LOWC_CASE
+    }
+    return ICV_ERR_UNSUPPORTED;
 }
 
 }  // namespace icv

@@ -12,7 +12,7 @@ enum PlanKind : int32_t {
     PLAN_INVALID = 0,
     PLAN_GENERIC = 1,   // vector-ALU kernel, any C, any dtype (on request)
     PLAN_MFMA = 2,      // tensor-core indirect GEMM, C a multiple of the k-granule
-    PLAN_MFMA_LOWC = 3, // tensor-core indirect GEMM for pixel rows of 8, 16 or 32 bytes (first-layer convolutions)
+    PLAN_MFMA_LOWC = 3, // tensor-core indirect GEMM for short pixel rows (first-layer convolutions)
     PLAN_MFMA_FREG = 4, // tensor-core indirect GEMM with the filter in registers and the input window in an LDS ring
     PLAN_MFMA_ANY = 5   // tensor-core indirect GEMM for rows of any length and alignment
 };
@@ -145,6 +145,7 @@ size_t freg_lds_bytes(int T, int KS, int PBK, int ring_rows);
 size_t patch_lds_bytes(int NR, int KCB, int ring, int cap_units, int ent_copies, int nbuf);
 int launch_igemm_lowc(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                       const int32_t* ind, const void* zero_row, void* out, bool a_direct, hipStream_t s);
+bool lowc_shape_supported(int dtype, int64_t row_bytes);
 // the any-channel-count kernel: tile for a problem (any_batch: independent of the batch size), bytes of its filter
 int choose_any_tile(int64_t M, int32_t K, int32_t row_bytes, bool any_batch);
 int64_t any_packed_bytes(const Geometry& g, int32_t row_bytes);

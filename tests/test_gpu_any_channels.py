@@ -67,3 +67,27 @@ def test_a_row_never_sees_its_neighbours(dtype, C):
     got = b2.output[0].cpu().numpy()
     assert np.isnan(got[hit]).all()
     assert np.array_equal(got[~hit], clean[0].cpu().numpy()[~hit])
+
+
+@pytest.mark.parametrize("plan", [0, icv.PLAN_PER_IMAGE, icv.PLAN_GATHER], ids=["auto", "per_image", "gather"])
+@pytest.mark.parametrize("k", [(3, 3), (7, 7), (5, 4)], ids=["3x3", "7x7", "5x4"])
+@pytest.mark.parametrize("dtype,C", [("bf16", 1), ("bf16", 2), ("bf16", 3), ("u8i8", 1), ("u8i8", 2), ("u8i8", 3), ("u8i8", 4),
+                                     ("f32", 1), ("f32", 2), ("f32", 3)])
+def test_first_layers_of_few_channels(dtype, C, k, plan):
+    """Rows of one to twelve bytes, whole and ragged paddings of the flattened reduction, pixels packed and apart."""
+    zp = 41 * C if dtype == "u8i8" else 0
+    s = ConvShape(f"first_{dtype}_c{C}", 3, 23, 19, C, 40 + 30 * (C % 2), *k, SY=2, SX=1 + C % 2, PT=k[0] // 2, PL=k[1] // 2,
+                  PB=1, PR=2, dtype=dtype, zero_point=zp, seed=650 + C)
+    x, w = make_tensors(s)
+    assert icv.plan_name(icv.make_params(s, plan=plan)).endswith("lowc_64x64")
+    buf, xd = run_indirect(s, x, w, plan=plan)
+    check_against_oracle(s, buf.output.cpu().numpy(), x, w)
+    out2, _ = run_im2col(s, buf, xd)
+    check_against_oracle(s, out2.cpu().numpy(), x, w)
+    stride = C + 1
+    apart = torch.full((3, 23, 19, stride), 9, dtype=torch.float32, device="cuda:0").to(xd.dtype)
+    apart[..., :C] = xd
+    b2 = icv.prepare(s, icv.to_device(w), plan=plan, in_pixel_stride=stride)
+    icv.run(b2, apart)
+    torch.cuda.synchronize()
+    assert torch.equal(b2.output, buf.output)
