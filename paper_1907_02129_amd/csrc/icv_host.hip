@@ -75,6 +75,12 @@ static const char* kAnyNames[3][4] = {
     {"generic_bf16_mfma_128x128", "generic_bf16_mfma_128x64", "generic_bf16_mfma_64x64", "generic_bf16_mfma_128x32"},
     {"generic_i8_mfma_128x128", "generic_i8_mfma_128x64", "generic_i8_mfma_64x64", "generic_i8_mfma_128x32"},
 };
+// what the split-reduction kernel takes from the plans with gathered rows, with a tile's pixel range, from the plain GEMM
+static const char* kSplitNames[3][3] = {
+    {"mfma_f32_split", "mfma_f32_patch_split", "gemm_f32_split"},
+    {"mfma_bf16_split", "mfma_bf16_patch_split", "gemm_bf16_split"},
+    {"mfma_i8_split", "mfma_i8_patch_split", "gemm_i8_split"},
+};
 static const char* kLowcNames[2][3] = {
     {"", "mfma_bf16_lowc_64x64", "mfma_i8_lowc_64x64"},
     {"generic_f32_lowc_64x64", "generic_bf16_lowc_64x64", "generic_i8_lowc_64x64"},     // rows of any alignment
@@ -124,13 +130,14 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     const int algo = p->plan & 7, plan_per_image = (p->plan >> 3) & 1;
     const int hook_tile = (p->plan >> 8) & 15, plan_ring = (p->plan >> 12) & 15, plan_per_cu = (p->plan >> 16) & 3,
               plan_kcb = (p->plan >> 18) & 3, plan_group = (p->plan >> 20) & 7;
+    const bool split_hook = hook_tile > kNumTileVariants;
     if (p->plan < 0 || p->plan >= (1 << 23) || (p->plan & 0xF0) != 0 || algo > ICV_PLAN_FILTER_REGS ||
-        hook_tile > kNumTileVariants || (hook_tile && algo == ICV_PLAN_VECTOR_ALU) || plan_ring == 1 || plan_ring > 12 ||
+        (hook_tile > kNumTileVariants && hook_tile != 9 && hook_tile != 10 && hook_tile != 15) || (hook_tile && algo == ICV_PLAN_VECTOR_ALU) || plan_ring == 1 || plan_ring > 12 ||
         plan_per_cu > 2 || plan_kcb > 2)
         return ICV_ERR_INVALID_ARG;
     // 0: the library chooses; 1: rows gathered per kernel element; 2: the tile's pixel range in LDS; 3: filter in registers
     const int plan_staging = algo == ICV_PLAN_GATHER ? 1 : (algo == ICV_PLAN_WINDOW ? 2 : (algo == ICV_PLAN_FILTER_REGS ? 3 : 0));
-    const int plan_kernel = algo == ICV_PLAN_VECTOR_ALU ? 1 : (hook_tile ? hook_tile + 1 : 0);
+    const int plan_kernel = algo == ICV_PLAN_VECTOR_ALU ? 1 : (hook_tile && !split_hook ? hook_tile + 1 : 0);
 
     const int64_t Hout = out_extent(p->Hin, p->PT, p->PB, p->DY, p->R, p->SY);
     const int64_t Wout = out_extent(p->Win, p->PL, p->PR, p->DX, p->S, p->SX);
@@ -374,8 +381,25 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         g->n_stages = g->T;
         g->name = kGenericNames[p->dtype];
     }
-    // the GEMM on the input tensor reads no entries, so it keeps the plain tiling
-    g->per_image = plan_per_image && !g->gemm_on_input ? 1 : 0;
+    // Too little work to fill the chip: the split-reduction kernel.  It reads the buffers of the filter-in-registers and
+    // the any-channel-count plans as they are; a problem of the other tensor-core plans, whose filter is laid out for
+    // their LDS stages, becomes one of the latter -- unless the buffer must serve every batch size.
+    g->split_tile = -1;
+    g->per_image = plan_per_image && !g->gemm_on_input ? 1 : 0;      // the GEMM on the input tensor reads no entries
+    if (plan_kernel == 0 && plan_staging == 0 && row_bytes >= 16 && T * row_bytes < (1ll << 31) && hook_tile != 15 &&
+        (g->kind == PLAN_MFMA_FREG || g->kind == PLAN_MFMA_ANY || (g->kind == PLAN_MFMA && !plan_per_image))) {
+        g->split_tile = split_hook ? hook_tile - 9 : choose_split(p, *g);
+        if (g->split_tile >= 0 && g->kind == PLAN_MFMA) {
+            g->name = kSplitNames[p->dtype][g->gemm_on_input ? 2 : (patch_rows ? 1 : 0)];
+            g->kind = PLAN_MFMA_ANY;
+            g->variant = kAnySplitTile;
+            g->MR = kAnyTiles[kAnySplitTile].MR;
+            g->NR = kAnyTiles[kAnySplitTile].NR;
+            g->KCB = 0; g->ring = 0; g->blocks_per_cu = 0; g->group = 0;
+            g->patch_rows = 0; g->zero_row_number = 0; g->cc_major = 0;
+            g->stages_per_tap = 1; g->taps_per_stage = 1; g->n_stages = g->T;
+        }
+    }
     g->img_rows = g->per_image ? Hout * Wout : M;
     g->img_tiles = (g->img_rows + g->MR - 1) / g->MR;
     g->image_bytes = g->per_image ? (int64_t)p->Hin * p->Win * stride_bytes : 0;
@@ -564,6 +588,10 @@ static int conv_common(const icv_conv_params* p, Geometry g, const void* a, cons
         g.ep.zp_shift = 128 - p->input_zero_point;
         g.ep_plain = false;
     }
+    if (g.split_tile >= 0 && !(a_direct && g.kind == PLAN_MFMA_FREG))
+        return launch_igemm_split(p, g, a, packed, ind, zero_row, out,
+                                  a_direct ? A_DENSE_WORKSPACE
+                                           : (is_plain_gemm(p) ? A_DENSE_INPUT : A_GATHERED), s);
     if (g.kind == PLAN_MFMA_FREG) return a_direct ? ICV_ERR_UNSUPPORTED : launch_igemm_freg(p, g, a, packed, ind, out, s);
     if (g.kind == PLAN_MFMA && g.patch_rows && !a_direct) return launch_igemm_patch(p, g, a, packed, ind, out, s);
     if (g.kind == PLAN_MFMA)

@@ -8,6 +8,7 @@ const TileVariant kAnyTiles[] = {
     {128, 64, 2, 2, "128x64"},
     {64, 64, 2, 2, "64x64"},
     {128, 32, 4, 1, "128x32"},
+    {32, 32, 1, 1, "split"},           // the split-reduction kernel alone
 };
 
 int choose_any_tile(int64_t M, int32_t K, int32_t row_bytes, bool any_batch)

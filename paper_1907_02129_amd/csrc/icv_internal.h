@@ -98,6 +98,7 @@ struct Geometry {
     int32_t cc_major;        // 1: stage = chunk * T + tap (channel chunks outermost), 0: stage = tap * chunks + chunk
     // filter-in-registers plan: column blocks per workgroup (1, 2, 4), row blocks per wavefront and pass, ring rows
     int32_t freg_wn, freg_mb, freg_ring;
+    int32_t split_tile;      // >= 0: tile of the split-reduction kernel, which then runs instead of the plan's own (same buffers)
     const char* name;
     EpilogueArgs ep;         // output stage of this call (plain: no bias, no ReLU, accumulator type)
     bool ep_plain;
@@ -151,6 +152,10 @@ int choose_any_tile(int64_t M, int32_t K, int32_t row_bytes, bool any_batch);
 int64_t any_packed_bytes(const Geometry& g, int32_t row_bytes);
 int launch_igemm_any(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                      const int32_t* ind, const void* zero_row, void* out, int a_mode, hipStream_t s);
+// the split-reduction kernel: its tile for a problem (-1: the problem is not one for it), and the launch
+int choose_split(const icv_conv_params* p, const Geometry& g);
+int launch_igemm_split(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
+                       const int32_t* ind, const void* zero_row, void* out, int a_mode, hipStream_t s);
 int launch_igemm_generic(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                          const int32_t* ind, const void* zero_row, void* out, bool a_direct, hipStream_t s);
 
@@ -161,11 +166,12 @@ struct TileVariant {
 };
 // Test hooks in icv_conv_params::plan above the public bits (icv.h says they must be 0; the library's own tests set
 // them to run every tile and pipeline shape on problems small enough for the CPU oracle): bits 8-11 tile
-// (1 + index into kTileVariants), bits 12-15 LDS ring depth of the gathering kernel (2..12), bits 16-17 workgroups
+// (1 + index into kTileVariants; 9 + tile of the split-reduction kernel, 15 never that kernel), bits 12-15 LDS ring depth of the gathering kernel (2..12), bits 16-17 workgroups
 // per compute unit (1, 2), bits 18-19 stage width (1: 64 bytes, 2: 128 bytes), bits 20-22 kernel elements per
 // pipeline stage of the pixel-range kernel.
 extern const TileVariant kTileVariants[];
 extern const int kNumTileVariants;
 extern const TileVariant kAnyTiles[];      // tiles of the any-channel-count kernel
+constexpr int kAnySplitTile = 4;           // ... and the entry of the split-reduction kernel's plans
 
 }  // namespace icv

@@ -379,8 +379,8 @@ int launch_build_indirection(const icv_conv_params* p, const Geometry& g, int32_
     a.R = p->R; a.S = p->S; a.SY = p->SY; a.SX = p->SX; a.DY = p->DY; a.DX = p->DX;
     a.PT = p->PT; a.PL = p->PL; a.MR = g.MR; a.T = g.T;
     a.stride_bytes = g.in_stride * g.elem_bytes;
-    if (g.MR != 64 && g.MR != 128 && g.MR != 256) return ICV_ERR_UNSUPPORTED;         // a tile's threads share a wavefront
-    a.quad_shift = g.MR == 64 ? 4 : (g.MR == 128 ? 5 : 6);
+    if (g.MR != 32 && g.MR != 64 && g.MR != 128 && g.MR != 256) return ICV_ERR_UNSUPPORTED;         // a tile's threads share a wavefront
+    a.quad_shift = g.MR == 32 ? 3 : (g.MR == 64 ? 4 : (g.MR == 128 ? 5 : 6));
     const int64_t threads = g.img_tiles << a.quad_shift;
     if (g.img_tiles > 0x7fffffffll || (threads + 255) / 256 > 0x7fffffffll) return ICV_ERR_UNSUPPORTED;
     a.n_tiles = (uint32_t)g.img_tiles;
