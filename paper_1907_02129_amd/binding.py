@@ -126,21 +126,22 @@ def _check(status: int, where: str):
         raise IcvError(status, where)
 
 
-def _ptr(t) -> ctypes.c_void_p:
-    if t is None:
-        return ctypes.c_void_p(0)
-    if isinstance(t, int):
-        return ctypes.c_void_p(t)
+# Device address and raw stream as plain integers, which ctypes converts by the functions' argument types: building a
+# c_void_p for each of five tensors and a torch Stream object per call was half of a small convolution's host time.
+def _ptr(t):
+    if t is None or isinstance(t, int):
+        return t
     if not t.is_cuda:
         raise ValueError("icv takes device tensors")
     if not t.is_contiguous():
         raise ValueError("icv takes contiguous tensors")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream=None) -> ctypes.c_void_p:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream(stream=None) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 # ---------------------------------------------------------------- thin wrappers, same names as the header
