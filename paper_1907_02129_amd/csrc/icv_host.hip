@@ -30,7 +30,7 @@ static int64_t out_extent(int64_t in, int64_t lo, int64_t hi, int64_t dil, int64
 static size_t packed_filter_base_bytes(const icv_conv_params* p, const Geometry& g)
 {
     if (g.kind == PLAN_MFMA_LOWC) return (size_t)g.n_tiles * g.NR * g.KCB;
-    if (g.kind == PLAN_MFMA_ANY) return (size_t)any_packed_bytes(g, p->C * g.elem_bytes);
+    if (g.kind == PLAN_MFMA_ANY || g.kind == PLAN_MFMA_WINDOW_SPLIT) return (size_t)any_packed_bytes(g, p->C * g.elem_bytes);
     return (size_t)g.n_tiles * g.NR * g.T * p->C * g.elem_bytes;
 }
 
@@ -80,6 +80,12 @@ static const char* kSplitNames[3][3] = {
     {"mfma_f32_split", "mfma_f32_patch_split", "gemm_f32_split"},
     {"mfma_bf16_split", "mfma_bf16_patch_split", "gemm_bf16_split"},
     {"mfma_i8_split", "mfma_i8_patch_split", "gemm_i8_split"},
+};
+// ... and with the window in LDS: from the plans with gathered rows, with a tile's pixel range
+static const char* kWindowSplitNames[3][2] = {
+    {"mfma_f32_64x64_split", "mfma_f32_64x64_patch_split"},
+    {"mfma_bf16_64x64_split", "mfma_bf16_64x64_patch_split"},
+    {"mfma_i8_64x64_split", "mfma_i8_64x64_patch_split"},
 };
 static const char* kLowcNames[2][3] = {
     {"", "mfma_bf16_lowc_64x64", "mfma_i8_lowc_64x64"},
@@ -132,7 +138,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
               plan_kcb = (p->plan >> 18) & 3, plan_group = (p->plan >> 20) & 7;
     const bool split_hook = hook_tile > kNumTileVariants;
     if (p->plan < 0 || p->plan >= (1 << 23) || (p->plan & 0xF0) != 0 || algo > ICV_PLAN_FILTER_REGS ||
-        (hook_tile > kNumTileVariants && hook_tile != 9 && hook_tile != 10 && hook_tile != 15) || (hook_tile && algo == ICV_PLAN_VECTOR_ALU) || plan_ring == 1 || plan_ring > 12 ||
+        (hook_tile > kNumTileVariants && (hook_tile < 9 || hook_tile > 11) && hook_tile != 15) || (hook_tile && algo == ICV_PLAN_VECTOR_ALU) || plan_ring == 1 || plan_ring > 12 ||
         plan_per_cu > 2 || plan_kcb > 2)
         return ICV_ERR_INVALID_ARG;
     // 0: the library chooses; 1: rows gathered per kernel element; 2: the tile's pixel range in LDS; 3: filter in registers
@@ -383,12 +389,29 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     }
     // Too little work to fill the chip: the split-reduction kernel.  It reads the buffers of the filter-in-registers and
     // the any-channel-count plans as they are; a problem of the other tensor-core plans, whose filter is laid out for
-    // their LDS stages, becomes one of the latter -- unless the buffer must serve every batch size.
+    // their LDS stages, becomes one of the latter or, with its window in LDS, one of its own -- unless the buffer must serve every batch
+    // size.
     g->split_tile = -1;
     g->per_image = plan_per_image && !g->gemm_on_input ? 1 : 0;      // the GEMM on the input tensor reads no entries
     if (plan_kernel == 0 && plan_staging == 0 && row_bytes >= 16 && T * row_bytes < (1ll << 31) && hook_tile != 15 &&
         (g->kind == PLAN_MFMA_FREG || g->kind == PLAN_MFMA_ANY || (g->kind == PLAN_MFMA && !plan_per_image))) {
         g->split_tile = split_hook ? hook_tile - 9 : choose_split(p, *g);
+        if (g->split_tile == kChooseWindow) {
+            g->split_tile = -1;
+            const int64_t span = tile_span_bound(p, Hout, Wout, 64);
+            if (g->kind == PLAN_MFMA && !plan_per_image && !g->gemm_on_input && row_bytes % 128 == 0 && span < 65535 &&
+                window_split_lds_bytes((int)T, row_bytes, span) <= 160 * 1024) {
+                g->name = kWindowSplitNames[p->dtype][patch_rows ? 1 : 0];
+                g->kind = PLAN_MFMA_WINDOW_SPLIT;
+                g->variant = kAnyTile64;         // what multiplies the patch matrix of the ablation by this filter
+                g->MR = kAnyTiles[kAnyTile64].MR;
+                g->NR = kAnyTiles[kAnyTile64].NR;
+                g->KCB = 0; g->ring = 0; g->blocks_per_cu = 0; g->group = 0; g->cc_major = 0;
+                g->patch_rows = (int32_t)span;
+                g->zero_row_number = (uint32_t)span;
+                g->stages_per_tap = 1; g->taps_per_stage = 1; g->n_stages = g->T;
+            }
+        }
         if (g->split_tile >= 0 && g->kind == PLAN_MFMA) {
             g->name = kSplitNames[p->dtype][g->gemm_on_input ? 2 : (patch_rows ? 1 : 0)];
             g->kind = PLAN_MFMA_ANY;
@@ -598,6 +621,8 @@ static int conv_common(const icv_conv_params* p, Geometry g, const void* a, cons
         return launch_igemm_mfma(p, g, a, packed, ind, zero_row, out,
                                  a_direct ? A_DENSE_WORKSPACE : (g.gemm_on_input ? A_DENSE_INPUT : A_GATHERED), s);
     if (g.kind == PLAN_MFMA_LOWC) return launch_igemm_lowc(p, g, a, packed, ind, zero_row, out, a_direct, s);
+    if (g.kind == PLAN_MFMA_WINDOW_SPLIT && !a_direct) return launch_igemm_window_split(p, g, a, packed, ind, out, s);
+    if (g.kind == PLAN_MFMA_WINDOW_SPLIT) return launch_igemm_any(p, g, a, packed, ind, zero_row, out, A_DENSE_WORKSPACE, s);
     if (g.kind == PLAN_MFMA_ANY)
         return launch_igemm_any(p, g, a, packed, ind, zero_row, out,
                                 a_direct ? A_DENSE_WORKSPACE

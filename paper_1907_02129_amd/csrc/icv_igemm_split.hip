@@ -21,7 +21,8 @@ static int slices_for(int64_t tiles, int64_t cus, int stages)
 // Measured, own kernel -> split kernel: one 7 x 7 image, 512 to 512 channels, 3x3: bf16 19.6 -> 8.7, uint8 15.6 -> 7.5, fp32 90.5
 // -> 15.8; batch 8 of it: 20.6 -> 12.2, 14.2 -> 9.5, 92.4 -> 37.4; one 14 x 14 image, 256 to 256: bf16 11.7 -> 6.9, fp32
 // 47.0 -> 11.5; 2 x 45 x 75, 64 to 64, fp32: 17.4 -> 13.8.  Past one round of the own kernel's tiles it loses: batch 64
-// of the first in bf16 takes 27.0 against 46.2.  The bfloat16 and uint8 filter-in-registers kernel stays ahead everywhere
+// of the first in bf16 takes 27.0 against 46.2.  With the window in LDS (icv_igemm_window_split.hip): batch 16 of the first
+// 21.0 -> 12.6, batch 32 21.4 -> 13.0 (uint8 15.6 -> 9.7), batch 64 25.0 against 25.2; 41 x 41, 320 to 208, 5x5 48.4 -> 17.8.  The bfloat16 and uint8 filter-in-registers kernel stays ahead everywhere
 // (5.4 against 6.7 on one 28 x 28 image, 128 to 128 channels).
 int choose_split(const icv_conv_params* p, const Geometry& g)
 {
@@ -43,7 +44,17 @@ int choose_split(const icv_conv_params* p, const Geometry& g)
         per_stage = f32 ? 0.61 : (p->dtype == ICV_U8I8 && g.patch_rows ? 0.3 : 0.22);
     }
     const int64_t own_tiles = images * ((img_rows + g.MR - 1) / g.MR) * ((p->K + g.NR - 1) / g.NR);
-    if (own_tiles > cus) return -1;
+    if (own_tiles > cus) {
+        // More than one round: in bf16 and uint8 only what measured slow there, tiles of 64 x 64 (two of them share a
+        // compute unit at 1.35 times the time of one) and rows gathered in 64-byte stages.  fp32 is bound by the matrix
+        // cores, whose work the tile's area counts.
+        const double area = (double)g.MR * g.NR / 4096.0;
+        if (g.kind != PLAN_MFMA) return -1;
+        if (f32) per_stage *= area * (double)own_tiles / cus;
+        else if (g.KCB == 64 && !g.patch_rows) per_stage *= area * (own_tiles > 2 * cus ? (double)own_tiles / (2 * cus) : 1.0);
+        else if (own_tiles <= 2 * cus && area == 1.0) per_stage *= 1.35;
+        else return -1;
+    }
     int best = -1;
     double best_time = 0.9 * (start + per_stage * stages);
     for (int tile = SPLIT_16; tile <= SPLIT_32; tile++) {
@@ -60,6 +71,16 @@ int choose_split(const icv_conv_params* p, const Geometry& g)
             t = 3.9 + (f32 ? 0.22 : 0.1) * longest + more * (0.35 + (f32 ? 0.21 : 0.09) * stages);
         }
         if (t < best_time) { best_time = t; best = tile; }
+    }
+    // the window in LDS: 64 x 64 tiles, one workgroup per compute unit
+    if (g.kind == PLAN_MFMA && !g.per_image && g.T >= 4 && row_bytes % 128 == 0) {
+        const int64_t span = tile_span_bound(p, g.Hout, g.Wout, 64);
+        if (span < 65535 && window_split_lds_bytes(g.T, row_bytes, span) <= kLdsPerCu) {
+            const int64_t tiles = ((g.M + 63) / 64) * ((p->K + 63) / 64);
+            const double rounds = (double)((tiles + cus - 1) / cus);
+            const double t = 1.2 + rounds * (4.0 + (f32 ? 0.6 : 0.1) * stages);
+            if (t < best_time) best = kChooseWindow;
+        }
     }
     return best;
 }

@@ -14,7 +14,8 @@ enum PlanKind : int32_t {
     PLAN_MFMA = 2,      // tensor-core indirect GEMM, C a multiple of the k-granule
     PLAN_MFMA_LOWC = 3, // tensor-core indirect GEMM for short pixel rows (first-layer convolutions)
     PLAN_MFMA_FREG = 4, // tensor-core indirect GEMM with the filter in registers and the input window in an LDS ring
-    PLAN_MFMA_ANY = 5   // tensor-core indirect GEMM for rows of any length and alignment
+    PLAN_MFMA_ANY = 5,  // tensor-core indirect GEMM for rows of any length and alignment
+    PLAN_MFMA_WINDOW_SPLIT = 6   // a tile's window in LDS, its reduction split over the wavefronts of a workgroup
 };
 
 // Output stage of icv_conv2d_nhwc_fused, as the kernels see it (icv_epilogue with the bias pointer typed by use).
@@ -152,7 +153,12 @@ int choose_any_tile(int64_t M, int32_t K, int32_t row_bytes, bool any_batch);
 int64_t any_packed_bytes(const Geometry& g, int32_t row_bytes);
 int launch_igemm_any(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                      const int32_t* ind, const void* zero_row, void* out, int a_mode, hipStream_t s);
-// the split-reduction kernel: its tile for a problem (-1: the problem is not one for it), and the launch
+// the split-reduction kernels: which of them takes a problem (-1: none; kChooseWindow: the one with the window in LDS, else
+// the tile of the other), and the launches
+constexpr int kChooseWindow = 2;
+size_t window_split_lds_bytes(int T, int64_t row_bytes, int64_t cap_rows);
+int launch_igemm_window_split(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
+                              const int32_t* ind, void* out, hipStream_t s);
 int choose_split(const icv_conv_params* p, const Geometry& g);
 int launch_igemm_split(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                        const int32_t* ind, const void* zero_row, void* out, int a_mode, hipStream_t s);
@@ -166,12 +172,13 @@ struct TileVariant {
 };
 // Test hooks in icv_conv_params::plan above the public bits (icv.h says they must be 0; the library's own tests set
 // them to run every tile and pipeline shape on problems small enough for the CPU oracle): bits 8-11 tile
-// (1 + index into kTileVariants; 9 + tile of the split-reduction kernel, 15 never that kernel), bits 12-15 LDS ring depth of the gathering kernel (2..12), bits 16-17 workgroups
+// (1 + index into kTileVariants; 9 + tile of the split-reduction kernel, 11 the one with the window in LDS, 15 never that kernel), bits 12-15 LDS ring depth of the gathering kernel (2..12), bits 16-17 workgroups
 // per compute unit (1, 2), bits 18-19 stage width (1: 64 bytes, 2: 128 bytes), bits 20-22 kernel elements per
 // pipeline stage of the pixel-range kernel.
 extern const TileVariant kTileVariants[];
 extern const int kNumTileVariants;
 extern const TileVariant kAnyTiles[];      // tiles of the any-channel-count kernel
+constexpr int kAnyTile64 = 2;              // ... the 64 x 64 one
 constexpr int kAnySplitTile = 4;           // ... and the entry of the split-reduction kernel's plans
 
 }  // namespace icv

@@ -138,7 +138,7 @@ int launch_pack_filter(const icv_conv_params* p, const Geometry& g, const void* 
                            (int32_t*)((uint8_t*)packed + g.wsum_offset), p->K, (int64_t)g.T * p->C);
         ICV_HIP_CHECK(hipGetLastError());
     }
-    if (g.kind == PLAN_MFMA_FREG || g.kind == PLAN_MFMA_ANY) {
+    if (g.kind == PLAN_MFMA_FREG || g.kind == PLAN_MFMA_ANY || g.kind == PLAN_MFMA_WINDOW_SPLIT) {
         const int64_t P = (CB + 15) / 16, total = g.n_tiles * (g.NR / 32) * ((g.T * P + 1) / 2) * 64;
         hipLaunchKernelGGL(k_pack_filter_frag, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
                            (const uint8_t*)filt, (uint8_t*)packed, p->K, g.T, (int)CB, total);

@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+import icv_layout as layout
 import plan_hooks as hooks
 from oracle import direct_conv as oracle
 from paper_1907_02129_amd import binding as icv
@@ -14,7 +15,7 @@ from paper_1907_02129_amd.workloads import ConvShape, make_tensors
 from test_gpu_parity import check_against_oracle, run_fused_case, run_im2col, run_indirect
 
 pytestmark = pytest.mark.gpu
-TILE16, TILE32, NEVER = hooks.tile(8), hooks.tile(9), hooks.tile(14)
+TILE16, TILE32, WINDOW, NEVER = hooks.tile(8), hooks.tile(9), hooks.tile(10), hooks.tile(14)
 
 
 def _shapes():
@@ -79,3 +80,39 @@ def test_infinite_weights_stay_in_their_channel(tile):
     others = [k for k in range(s.K) if k != 7]
     assert torch.equal(buf.output[..., others], clean[..., others])
     assert not np.isfinite(buf.output[..., 7].cpu().numpy()).any()
+
+
+def _window_shapes():
+    mk = ConvShape
+    out = []
+    # fewer stages than wavefronts, as many, more; windows that cross images and rows; ragged K; strides and dilations
+    for i, (dtype, n, h, w, C, K, r, s) in enumerate([
+            ("bf16", 3, 7, 7, 512, 70, 3, 3), ("bf16", 2, 14, 13, 256, 64, 3, 3), ("bf16", 1, 9, 30, 64, 33, 5, 5), ("bf16", 2, 5, 6, 192, 130, 2, 2),
+            ("u8i8", 5, 7, 7, 512, 40, 3, 3), ("u8i8", 2, 11, 17, 128, 65, 5, 5), ("u8i8", 1, 6, 5, 384, 8, 2, 3),
+            ("f32", 2, 7, 9, 96, 31, 3, 3), ("f32", 1, 13, 12, 32, 64, 5, 5), ("f32", 3, 4, 4, 160, 20, 2, 2)]):
+        zp = (0, 128, 77)[i % 3] if dtype == "u8i8" else 0
+        for sy, dx, pad in ((1, 1, 1), (2, 2, 3)):
+            out.append(mk(f"win_{dtype}_c{C}_{r}x{s}_s{sy}", n, h, w, C, K, r, s, SY=sy, SX=sy, DX=dx, PT=pad, PL=pad, PB=pad, PR=pad,
+                          dtype=dtype, zero_point=zp, seed=750 + i))
+    return out
+
+
+@pytest.mark.parametrize("s", _window_shapes(), ids=lambda s: s.name)
+def test_window_split_matches_oracle(s):
+    p = icv.make_params(s, plan=WINDOW)
+    name = icv.plan_name(p)
+    print("conv", s.name, name, flush=True)
+    x, w = make_tensors(s)
+    buf, xd = run_indirect(s, x, w, plan=WINDOW)
+    check_against_oracle(s, buf.output.cpu().numpy(), x, w)
+    # (a window that does not fit LDS beside the entries stays with its own plan)
+    fits = s.name != "win_bf16_c512_3x3_s2"
+    assert (name.startswith("mfma_") and "64x64" in name and name.endswith("split")) == fits, name
+    if fits:
+        got, tail = layout.logical_indirection(p, buf.indirection, s.N * buf.Hout * buf.Wout)
+        assert np.array_equal(got, oracle.indirection(s)) and np.all(tail == -1)
+        out2, _ = run_im2col(s, buf, xd)
+        check_against_oracle(s, out2.cpu().numpy(), x, w)
+    acc, mag = oracle.conv2d_abs(s, x, w) if s.dtype != "u8i8" else (oracle.conv2d_u8i8(s, x, w, s.zero_point), None)
+    for stride in (0, s.K + 3):
+        run_fused_case(s, x, w, acc, mag, True, True, plan=WINDOW, out_pixel_stride=stride)
