@@ -31,27 +31,24 @@ int choose_split(const icv_conv_params* p, const Geometry& g)
     const int64_t row_bytes = (int64_t)p->C * g.elem_bytes;
     const double stages = (double)((g.T * ((row_bytes + 15) / 16) + 7) / 8);
     const int64_t images = g.per_image ? p->N : 1, img_rows = g.per_image ? (int64_t)g.Hout * g.Wout : g.M;
+    const bool rows = g.kind == PLAN_MFMA && !g.patch_rows && !g.gemm_on_input;      // goes to the any-channel-count kernel
     double start = 3.7, per_stage;
     if (g.kind == PLAN_MFMA_FREG) {
         if (!f32) return -1;
         per_stage = 0.7;
-    } else if (g.kind == PLAN_MFMA_ANY) {
+    } else if (g.kind == PLAN_MFMA_ANY || rows) {
         start = 2.9;
         per_stage = f32 ? 0.7 : 0.42;
-    } else if (g.KCB == 64 && !g.patch_rows) {
-        per_stage = f32 ? 0.95 : 0.5;
     } else {
         per_stage = f32 ? 0.61 : (p->dtype == ICV_U8I8 && g.patch_rows ? 0.3 : 0.22);
     }
     const int64_t own_tiles = images * ((img_rows + g.MR - 1) / g.MR) * ((p->K + g.NR - 1) / g.NR);
     if (own_tiles > cus) {
         // More than one round: in bf16 and uint8 only what measured slow there, tiles of 64 x 64 (two of them share a
-        // compute unit at 1.35 times the time of one) and rows gathered in 64-byte stages.  fp32 is bound by the matrix
-        // cores, whose work the tile's area counts.
+        // compute unit at 1.35 times the time of one).  fp32 is bound by the matrix cores, whose work the tile's area counts.
         const double area = (double)g.MR * g.NR / 4096.0;
-        if (g.kind != PLAN_MFMA) return -1;
+        if (g.kind != PLAN_MFMA || (rows && !f32)) return -1;
         if (f32) per_stage *= area * (double)own_tiles / cus;
-        else if (g.KCB == 64 && !g.patch_rows) per_stage *= area * (own_tiles > 2 * cus ? (double)own_tiles / (2 * cus) : 1.0);
         else if (own_tiles <= 2 * cus && area == 1.0) per_stage *= 1.35;
         else return -1;
     }

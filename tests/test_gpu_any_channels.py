@@ -91,3 +91,21 @@ def test_first_layers_of_few_channels(dtype, C, k, plan):
     icv.run(b2, apart)
     torch.cuda.synchronize()
     assert torch.equal(b2.output, buf.output)
+
+
+@pytest.mark.parametrize("plan", [0, icv.PLAN_PER_IMAGE], ids=["auto", "per_image"])
+@pytest.mark.parametrize("dtype,C,K", [("bf16", 96, 140), ("bf16", 96, 64), ("bf16", 160, 24), ("u8i8", 192, 70), ("f32", 48, 33)])
+def test_aligned_rows_that_are_gathered_per_kernel_element(dtype, C, K, plan):
+    """Rows of whole 64-byte units that no power of two fits take the same kernel: every tile, two strides, pixels apart."""
+    s = ConvShape(f"rows_{dtype}_{C}", 5, 45, 47, C, K, 3, 3, SY=1 + (K == 24), PT=1, PL=1, PB=1, PR=1, dtype=dtype,
+                  zero_point=11 if dtype == "u8i8" else 0, seed=670)
+    name = icv.plan_name(icv.make_params(s, plan=plan))
+    print("conv", s.name, name, flush=True)
+    assert name.startswith("mfma_") and ("_rows_" in name or name.endswith("_split"))
+    x, w = make_tensors(s)
+    buf, xd = run_indirect(s, x, w, plan=plan)
+    check_against_oracle(s, buf.output.cpu().numpy(), x, w)
+    gathered, _ = run_indirect(s, x, w, plan=icv.PLAN_GATHER | plan)
+    check_against_oracle(s, gathered.output.cpu().numpy(), x, w)
+    out2, _ = run_im2col(s, buf, xd)
+    check_against_oracle(s, out2.cpu().numpy(), x, w)
