@@ -429,7 +429,9 @@ int launch_igemm_lowc(const icv_conv_params* p, const Geometry& g, const void* i
     int teams = 1;
     if (!a_direct && a.rows && g.T <= batch_taps) {
         const int fit = (int)((kLdsPerCu - b_bytes) / a_bytes);
-        const int want = unit <= 8 ? 4 : 2;
+        // fp32 rows of two and three floats: single teams too.  The matrix cores bound them, and two workgroups, unlike the
+        // teams of one, multiply and move at different times (16 x 224 x 224, 3 channels, 7x7: 51.1 against 56.5 us).
+        const int want = p->dtype == ICV_F32 && unit >= 8 ? 1 : (unit <= 8 ? 4 : 2);
         teams = fit >= want ? want : (fit >= 2 ? 2 : 1);
     }
     const size_t lds_bytes = b_bytes + teams * a_bytes;
