@@ -370,7 +370,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     } else if (plan_kernel != 1 && T * row_bytes < (1ll << 31)) {
         // rows of any other length or alignment
         g->kind = PLAN_MFMA_ANY;
-        g->variant = choose_any_tile(M, p->K, (int32_t)row_bytes, T * row_bytes, f32, plan_per_image);
+        g->variant = choose_any_tile(M, p->K, (int32_t)row_bytes, T * row_bytes, p->dtype, plan_per_image);
         g->MR = kAnyTiles[g->variant].MR;
         g->NR = kAnyTiles[g->variant].NR;
         g->KCB = 0;
@@ -435,7 +435,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     if (g->kind == PLAN_MFMA && !g->patch_rows && !g->gemm_on_input && plan_kernel == 0 && plan_staging == 0 && hook_tile != 15 &&
         T * row_bytes < (1ll << 31)) {
         g->kind = PLAN_MFMA_ANY;
-        g->variant = choose_any_tile(M, p->K, (int32_t)row_bytes, T * row_bytes, f32, plan_per_image);
+        g->variant = choose_any_tile(M, p->K, (int32_t)row_bytes, T * row_bytes, p->dtype, plan_per_image);
         g->MR = kAnyTiles[g->variant].MR;
         g->NR = kAnyTiles[g->variant].NR;
         g->KCB = 0; g->ring = 0; g->blocks_per_cu = 0; g->group = 0; g->cc_major = 0;

@@ -11,19 +11,26 @@ const TileVariant kAnyTiles[] = {
     {32, 32, 1, 1, "split"},           // the split-reduction kernel alone
 };
 
-int choose_any_tile(int64_t M, int32_t K, int32_t row_bytes, int64_t patch_bytes, bool f32, bool any_batch)
+int choose_any_tile(int64_t M, int32_t K, int32_t row_bytes, int64_t patch_bytes, int32_t dtype, bool any_batch)
 {
     if (row_bytes < 16) return 2;      // rows shorter than a piece: built for this tile only
     if (K <= 32) return 3;
-    const int wide = K <= 64 ? 1 : 0;
+    const bool f32 = dtype == ICV_F32;
+    // 64 columns also where 128 would leave half of the last column tile empty.  192 columns, 128 x 64 against 128 x 128: 48
+    // channels, 128 x 27 x 27: uint8 24.8 against 34.3 us, fp32 134.2 against 168.0, bf16 32.5 against 33.3; 96 channels, 16 x 56 x 56: bf16
+    // 28.3 against 32.9.  In bf16 not for patches over 4 KB (100 channels, 5x5: 52.4 against 51.6) nor, at any batch, past 256
+    // columns (320: 44.7 against 40.2), where the rows are read too often.
+    bool half = K > 64 && K < 512 && K % 128 != 0 && K % 128 <= 64;
+    if (dtype == ICV_BF16) half = half && (K < 256 ? patch_bytes < 4096 : !any_batch);
+    const int wide = K <= 64 || half ? 1 : 0;
     // 64 x 64 when the wider tile leaves most of the chip with a single workgroup or none: two and more per compute
     // unit are what hides this kernel's latencies.  fp32, bound by the matrix cores, wants two everywhere.  Measured with 128 x 128
     // against 64 x 64, bf16 (uint8): 392 tiles, 192 channels, 3x3: 30.9 against 44.5 us (20.5 against 25.5); 400 tiles, 384 channels: 58.2
     // against 88.0 (35.3 against 46.1); 294 tiles, 320 channels, 5x5: 117.9 against 117.3 (72.8 against 58.6); 281 tiles: 35.5
     // against 38.4 (27.4 against 23.6).  fp32, 392 tiles: 218.9 against 210.3; uint8, 344
-    // tiles of a reduction of only 496: 16.2 against 12.9.  A batch-independent buffer's layout must not depend on N.
+    // tiles of a reduction of only 496: 16.2 against 12.9; fp32, 549 tiles of 128 x 64: 257.5 against 221.8.  A batch-independent buffer's layout must not depend on N.
     const int64_t tiles = ((M + 127) / 128) * ((K + kAnyTiles[wide].NR - 1) / kAnyTiles[wide].NR);
-    return any_batch || tiles >= (f32 || wide || patch_bytes < 1000 ? 512 : 336) ? wide : 2;
+    return any_batch || tiles >= (f32 && half ? 1024 : (f32 || K <= 64 || patch_bytes < 1000 ? 512 : 336)) ? wide : 2;
 }
 
 int64_t any_packed_bytes(const Geometry& g, int32_t row_bytes)

@@ -15,8 +15,8 @@
 //    need: with 128 x 128 tiles every B fragment is used for four MFMAs (32 bytes per clock of the 64 that L1 gives)
 //    and every A fragment for one (128 bytes per clock, all that LDS gives).
 //
-// Measured (graph replays, one launch): 48 bfloat16 channels, 128 images of 27 x 27, 192 output channels, 3x3: 44.8 us,
-// 346 TFLOP/s, where the vector ALUs took 2344 us; 416 uint8 channels, 2 x 78 x 78, 120 output channels: 19.3 us, 565
+// Measured (graph replays, one launch): 48 bfloat16 channels, 128 images of 27 x 27, 192 output channels, 3x3: 32.5 us,
+// 476 TFLOP/s (128 x 64 tiles; 33.3 with 128 x 128), where the vector ALUs took 2344 us; 416 uint8 channels, 2 x 78 x 78, 120 output channels: 19.3 us, 565
 // TOP/s; 3 fp32 channels, 16 images of 224 x 224, 7x7 stride 2, whose 12-byte rows are padded to a piece: 120 us from
 // 1115 us.
 //

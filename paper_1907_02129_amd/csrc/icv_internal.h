@@ -149,7 +149,7 @@ int launch_igemm_lowc(const icv_conv_params* p, const Geometry& g, const void* i
                       const int32_t* ind, const void* zero_row, void* out, bool a_direct, hipStream_t s);
 bool lowc_shape_supported(int dtype, int64_t row_bytes);
 // the any-channel-count kernel: tile for a problem (any_batch: independent of the batch size), bytes of its filter
-int choose_any_tile(int64_t M, int32_t K, int32_t row_bytes, int64_t patch_bytes, bool f32, bool any_batch);
+int choose_any_tile(int64_t M, int32_t K, int32_t row_bytes, int64_t patch_bytes, int32_t dtype, bool any_batch);
 int64_t any_packed_bytes(const Geometry& g, int32_t row_bytes);
 int launch_igemm_any(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                      const int32_t* ind, const void* zero_row, void* out, int a_mode, hipStream_t s);
