@@ -84,7 +84,8 @@ typedef struct icv_conv_params {
  * relative to that image's first pixel, and row tiles never straddle two images; the kernels add
  * n * Hin*Win*pixel stride for image n.  Section 2.3 lists a change of batch size among the events that force the
  * buffer to be (partly) rebuilt; with this bit none is needed: a buffer built with any N serves every N, and N
- * plays no part in the choice of the tile (the packed filter and zero row do not depend on N either).  The price
+ * plays no part in the choice of their layout (the packed filter and zero row do not depend on N either; which of the
+ * kernels that read that layout runs may depend on it).  The price
  * is a partial last tile per image instead of one per batch. */
 #define ICV_PLAN_PER_IMAGE 8
 
@@ -257,7 +258,19 @@ ICV_API int icv_conv2d_nhwc_im2col_static(const icv_conv_params* p, const void* 
 ICV_API int icv_measure_mfma_peak(int32_t dtype, int32_t waves_per_simd, int32_t varied_operands, double* ops_per_second,
                                   void* stream);
 
-/* Name of the kernel variant icv_conv2d_nhwc would launch for p (static string; "" when invalid). */
+/*
+ * Name of the kernel variant icv_conv2d_nhwc would launch for p (static string; "" when invalid):
+ *   generic_<type>                     the vector-ALU kernel
+ *   gemm_<type>_<tile>...              the plain GEMM on the input tensor (1x1, stride 1, no padding)
+ *   mfma_<type>_freg_w<n>m<m>          filter in registers
+ *   mfma_<type>_<tile>..._patch        the tile's pixel range in LDS
+ *   mfma_<type>_<tile>..._p<n>         rows gathered per kernel element, aligned rows
+ *   mfma_<type>_any_<tile>             rows gathered per kernel element, rows of any length and alignment
+ *   mfma_<type>_lowc_<tile>            very short rows, the whole reduction gathered at once
+ *   mfma_|gemm_<type>_split_<tile>     the reduction of a tile split over the wavefronts of a workgroup
+ *   mfma_<type>_<tile>_window_split    the same with the tile's pixel range in LDS
+ * With ICV_PLAN_PER_IMAGE the kernel may differ with N where it reads the same buffers.
+ */
 ICV_API const char* icv_plan_name(const icv_conv_params* p);
 
 ICV_API const char* icv_status_string(int status);

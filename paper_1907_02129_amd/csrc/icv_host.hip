@@ -71,32 +71,18 @@ static bool is_plain_gemm(const icv_conv_params* p)
 
 static const char* kGenericNames[3] = {"generic_f32", "generic_bf16", "generic_u8i8"};
 static const char* kAnyNames[3][4] = {
-    {"generic_f32_mfma_128x128", "generic_f32_mfma_128x64", "generic_f32_mfma_64x64", "generic_f32_mfma_128x32"},
-    {"generic_bf16_mfma_128x128", "generic_bf16_mfma_128x64", "generic_bf16_mfma_64x64", "generic_bf16_mfma_128x32"},
-    {"generic_i8_mfma_128x128", "generic_i8_mfma_128x64", "generic_i8_mfma_64x64", "generic_i8_mfma_128x32"},
+    {"mfma_f32_any_128x128", "mfma_f32_any_128x64", "mfma_f32_any_64x64", "mfma_f32_any_128x32"},
+    {"mfma_bf16_any_128x128", "mfma_bf16_any_128x64", "mfma_bf16_any_64x64", "mfma_bf16_any_128x32"},
+    {"mfma_i8_any_128x128", "mfma_i8_any_128x64", "mfma_i8_any_64x64", "mfma_i8_any_128x32"},
 };
-// what the split-reduction kernel takes from the plans with gathered rows, with a tile's pixel range, from the plain GEMM
-static const char* kSplitNames[3][3] = {
-    {"mfma_f32_split", "mfma_f32_patch_split", "gemm_f32_split"},
-    {"mfma_bf16_split", "mfma_bf16_patch_split", "gemm_bf16_split"},
-    {"mfma_i8_split", "mfma_i8_patch_split", "gemm_i8_split"},
+// the split-reduction kernel, [dtype][1: instead of the plain GEMM on the input][tile]
+static const char* kSplitNames[3][2][2] = {
+    {{"mfma_f32_split_16x16", "mfma_f32_split_32x32"}, {"gemm_f32_split_16x16", "gemm_f32_split_32x32"}},
+    {{"mfma_bf16_split_16x16", "mfma_bf16_split_32x32"}, {"gemm_bf16_split_16x16", "gemm_bf16_split_32x32"}},
+    {{"mfma_i8_split_16x16", "mfma_i8_split_32x32"}, {"gemm_i8_split_16x16", "gemm_i8_split_32x32"}},
 };
-// ... and with the window in LDS: from the plans with gathered rows, with a tile's pixel range
-static const char* kWindowSplitNames[3][2] = {
-    {"mfma_f32_64x64_split", "mfma_f32_64x64_patch_split"},
-    {"mfma_bf16_64x64_split", "mfma_bf16_64x64_patch_split"},
-    {"mfma_i8_64x64_split", "mfma_i8_64x64_patch_split"},
-};
-// aligned rows gathered per kernel element through the any-channel-count kernel
-static const char* kRowNames[3][4] = {
-    {"mfma_f32_rows_128x128", "mfma_f32_rows_128x64", "mfma_f32_rows_64x64", "mfma_f32_rows_128x32"},
-    {"mfma_bf16_rows_128x128", "mfma_bf16_rows_128x64", "mfma_bf16_rows_64x64", "mfma_bf16_rows_128x32"},
-    {"mfma_i8_rows_128x128", "mfma_i8_rows_128x64", "mfma_i8_rows_64x64", "mfma_i8_rows_128x32"},
-};
-static const char* kLowcNames[2][3] = {
-    {"", "mfma_bf16_lowc_64x64", "mfma_i8_lowc_64x64"},
-    {"generic_f32_lowc_64x64", "generic_bf16_lowc_64x64", "generic_i8_lowc_64x64"},     // rows of any alignment
-};
+static const char* kWindowSplitNames[3] = {"mfma_f32_64x64_window_split", "mfma_bf16_64x64_window_split", "mfma_i8_64x64_window_split"};
+static const char* kLowcNames[3] = {"mfma_f32_lowc_64x64", "mfma_bf16_lowc_64x64", "mfma_i8_lowc_64x64"};
 // filter in registers: [dtype][column blocks per workgroup 1, 2, 4][row blocks per wavefront and pass 1, 2]
 static const char* kFregNames[3][3][2] = {
     {{"mfma_f32_freg_w1m1", "mfma_f32_freg_w1m2"}, {"mfma_f32_freg_w2m1", "mfma_f32_freg_w2m2"},
@@ -333,7 +319,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         g->stages_per_tap = 1;
         g->taps_per_stage = g->T;
         g->n_stages = 1;
-        g->name = kLowcNames[lowc_words ? 0 : 1][p->dtype];
+        g->name = kLowcNames[p->dtype];
         // compact entries (16-bit pixel numbers inside the tile's range) when every tile's range is short enough;
         // plan "rows gathered per kernel element" keeps the int32 offsets, for comparison
         const int64_t span = tile_span_bound(p, Hout, Wout, 64);
@@ -407,7 +393,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
             const int64_t span = tile_span_bound(p, Hout, Wout, 64);
             if (g->kind == PLAN_MFMA && !plan_per_image && !g->gemm_on_input && row_bytes % 128 == 0 && span < 65535 &&
                 window_split_lds_bytes((int)T, row_bytes, span) <= 160 * 1024) {
-                g->name = kWindowSplitNames[p->dtype][patch_rows ? 1 : 0];
+                g->name = kWindowSplitNames[p->dtype];
                 g->kind = PLAN_MFMA_WINDOW_SPLIT;
                 g->variant = kAnyTile64;         // what multiplies the patch matrix of the ablation by this filter
                 g->MR = kAnyTiles[kAnyTile64].MR;
@@ -419,7 +405,6 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
             }
         }
         if (g->split_tile >= 0 && g->kind == PLAN_MFMA) {
-            g->name = kSplitNames[p->dtype][g->gemm_on_input ? 2 : (patch_rows ? 1 : 0)];
             g->kind = PLAN_MFMA_ANY;
             g->variant = kAnySplitTile;
             g->MR = kAnyTiles[kAnySplitTile].MR;
@@ -428,6 +413,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
             g->patch_rows = 0; g->zero_row_number = 0; g->cc_major = 0;
             g->stages_per_tap = 1; g->taps_per_stage = 1; g->n_stages = g->T;
         }
+        if (g->split_tile >= 0) g->name = kSplitNames[p->dtype][g->gemm_on_input][g->split_tile];
     }
     // Rows gathered per kernel element (no pixel range in LDS) go through the any-channel-count kernel, which keeps the filter
     // out of LDS: 8 x 67 x 67, 224 to 96 channels, 3x3: 49.0 -> 36 us in bf16 and 247.7 -> 178 in fp32; 16 x 40 x 40, 384 to 256: 64.4 -> 58 in
@@ -440,7 +426,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         g->NR = kAnyTiles[g->variant].NR;
         g->KCB = 0; g->ring = 0; g->blocks_per_cu = 0; g->group = 0; g->cc_major = 0;
         g->stages_per_tap = 1; g->taps_per_stage = 1; g->n_stages = g->T;
-        g->name = kRowNames[p->dtype][g->variant];
+        g->name = kAnyNames[p->dtype][g->variant];
     }
     g->img_rows = g->per_image ? Hout * Wout : M;
     g->img_tiles = (g->img_rows + g->MR - 1) / g->MR;

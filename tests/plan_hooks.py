@@ -22,3 +22,14 @@ KCB64 = 1 << 18
 
 def group(taps: int) -> int:
     return taps << 20
+
+
+NO_SPLIT = tile(14)      # neither a split-reduction kernel nor, for aligned rows, the any-channel-count one: the plan's own kernel
+
+
+def family(name: str) -> str:
+    """The kernel a plan name stands for (icv.h lists the names)."""
+    for f in ("window_split", "split", "any", "lowc", "freg", "patch"):
+        if f in name:
+            return f
+    return {"gene": "vector_alu", "gemm": "gemm", "mfma": "gather"}[name[:4]]

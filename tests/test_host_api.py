@@ -173,7 +173,7 @@ def test_status_strings(lib):
 
 
 def test_plans(lib):
-    assert icv.plan_name(icv.make_params(CONFIGS["cfg1_tiny_f32"])).startswith("generic")
+    assert icv.plan_name(icv.make_params(CONFIGS["cfg1_tiny_f32"], plan=icv.PLAN_VECTOR_ALU)) == "generic_f32"
     assert icv.plan_name(icv.make_params(CONFIGS["cfg2_3x3_c64"])).startswith("mfma_bf16")
     assert icv.plan_name(icv.make_params(CONFIGS["cfg4_int8_3x3"])).startswith("mfma_i8")
     # any uint8 zero point runs on the tensor cores; the packed filter then carries K int32 filter sums behind it
@@ -185,9 +185,32 @@ def test_plans(lib):
     # 1x1 stride 1 without padding is a plain GEMM on the input tensor (section 3.2's advice to switch primitives)
     assert icv.plan_name(icv.make_params(CONFIGS["cfg5a_1x1"])).startswith("gemm_bf16")
     assert icv.plan_name(icv.make_params(CONFIGS["cfg5a_1x1"].with_(SX=2, SY=2))).startswith("mfma_bf16")
-    # odd channel counts fall back to the vector-ALU kernel instead of failing
+    # odd channel counts run on the tensor cores too, through the kernel for rows of any length
     odd = ConvShape("odd", 1, 8, 8, 5, 3, 3, 3)
-    assert icv.plan_name(icv.make_params(odd)).startswith("generic")
+    assert icv.plan_name(icv.make_params(odd)) == "mfma_bf16_any_64x64"
+
+
+def test_plan_names_tell_the_kernels_apart(lib):
+    """A plan name stands for the kernel that is launched: where a split-reduction kernel takes a problem over, whatever
+    plan's buffers it reads, the name is its own; only the vector-ALU kernel is called generic."""
+    import plan_hooks as hooks
+    freg32 = ConvShape("n_freg32", 2, 45, 75, 64, 64, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="f32")
+    tail = ConvShape("n_any", 1, 8, 8, 37, 8, 3, 3, PT=1, PL=1, PB=1, PR=1)
+    point = ConvShape("n_gemm", 2, 21, 13, 256, 64, 1, 1)
+    gather = ConvShape("n_gather", 2, 13, 17, 96, 40, 3, 3, PT=1, PL=1, PB=1, PR=1)
+    window = ConvShape("n_window", 32, 7, 7, 512, 512, 3, 3, PT=1, PL=1, PB=1, PR=1)
+    for s, split, own in ((freg32, "mfma_f32_split_32x32", "freg"), (tail, "mfma_bf16_split_16x16", "any"),
+                          (point, "gemm_bf16_split_16x16", "gemm"), (gather, "mfma_bf16_split_16x16", "gather"),
+                          (window, "mfma_bf16_64x64_window_split", "patch")):
+        assert icv.plan_name(icv.make_params(s)) == split, s.name
+        assert hooks.family(icv.plan_name(icv.make_params(s, plan=hooks.NO_SPLIT))) == own, s.name
+        assert icv.plan_name(icv.make_params(s, plan=icv.PLAN_VECTOR_ALU)) == {"f32": "generic_f32", "bf16": "generic_bf16"}[s.dtype]
+    for tile, name in ((8, "split_16x16"), (9, "split_32x32")):
+        for s in (freg32, tail, point, gather):
+            assert icv.plan_name(icv.make_params(s, plan=hooks.tile(tile))).endswith(name)
+    for dtype, C in (("bf16", 3), ("u8i8", 1), ("f32", 3)):
+        s = ConvShape("n_lowc", 1, 224, 224, C, 64, 7, 7, SY=2, SX=2, PT=3, PL=3, PB=3, PR=3, dtype=dtype)
+        assert hooks.family(icv.plan_name(icv.make_params(s))) == "lowc"
 
 
 def _exact_span(shape, rows):
