@@ -291,7 +291,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         return ICV_ERR_UNSUPPORTED;
     }
     // very short rows (first-layer convolutions): the whole reduction of a tile is gathered at once
-    const bool lowc_words = p->dtype != ICV_F32 && (row_bytes == 8 || row_bytes == 16 || row_bytes == 32);
+    const bool lowc_words = short_row_words(p->dtype, row_bytes);
     const bool lowc_ok = plan_kernel == 0 && lowc_shape_supported(p->dtype, row_bytes) &&
                          (!lowc_words || stride_bytes % row_bytes == 0) && T * row_bytes <= 608;
     g->freg_wn = freg_wn; g->freg_mb = freg_mb; g->freg_ring = freg_ring;
@@ -527,9 +527,7 @@ size_t icv_im2col_bytes(const icv_conv_params* p)
 {
     Geometry g;
     if (make_ablation_geometry(p, &g) != ICV_OK) return 0;
-    // rows padded to whole tiles so the GEMM kernel may read (and discard) the rows past M
-    if (g.kind == PLAN_MFMA_LOWC) return (size_t)g.m_tiles * g.MR * g.KCB;
-    return (size_t)g.m_tiles * g.MR * g.T * p->C * g.elem_bytes;
+    return (size_t)(patch_matrix_rows(g) * patch_matrix_row_bytes(p, g));
 }
 
 int64_t icv_indirection_index(const icv_conv_params* p, int64_t m, int32_t tap)

@@ -50,7 +50,7 @@ int launch_igemm_any(const icv_conv_params* p, const Geometry& g, const void* in
     a.out = out;
     a.row_bytes = p->C * g.elem_bytes;
     a.a_row_stride = a_mode == A_DENSE_WORKSPACE ? (int64_t)g.T * a.row_bytes : (int64_t)g.in_stride * g.elem_bytes;
-    a.a_rows = a_mode == A_DENSE_WORKSPACE ? g.m_tiles * g.MR : g.M;
+    a.a_rows = a_mode == A_DENSE_WORKSPACE ? patch_matrix_rows(g) : g.M;
     a.image_bytes = a_mode == A_GATHERED ? g.image_bytes : 0;
     a.img_tiles = (uint32_t)g.img_tiles;
     a.img_rows = (uint32_t)g.img_rows;

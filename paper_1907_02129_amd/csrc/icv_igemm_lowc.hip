@@ -36,7 +36,7 @@ struct LowcArgs {
     int32_t stride_bytes;   // bytes between input pixels
     int32_t col_blocks;     // 32-column blocks per workgroup (blockIdx.y selects the group)
     int32_t k_rows;         // rows of the packed filter (K padded to 64)
-    int32_t direct;         // 1: `a` is the dense patch matrix [rows][KP] of the ablation path
+    int32_t direct;         // 1: `a` is the dense patch matrix of the ablation path, rows of KP bytes (of T * U: shorter rows)
     uint32_t zero_fill;     // four bytes of the zero row: zeros, or the zero point of uint8 activations
     EpilogueArgs ep;
 };
@@ -330,11 +330,18 @@ __global__ __launch_bounds__(256 * TEAMS) void k_igemm_lowc(LowcArgs g)
     for (int64_t mt = blockIdx.x; mt < g.m_tiles; mt += G) {
         __syncthreads();      // previous tile's fragment reads are done (first pass: filter and padding are in)
         if (g.direct) {
-            const uint8_t* src = g.a + mt * MR * (int64_t)g.KP;
-            const int vec_per_row = g.KP / 16;
-            for (int v = tid; v < MR * vec_per_row; v += 256) {
-                const int row = v / vec_per_row, c = v - row * vec_per_row;
-                *(uint4*)(ldsA + row * pitch + c * 16) = *(const uint4*)(src + (int64_t)row * g.KP + c * 16);
+            if constexpr (DT != ICV_F32 && U % 8 == 0) {      // rows of KP bytes
+                const uint8_t* src = g.a + mt * MR * (int64_t)g.KP;
+                const int vec_per_row = g.KP / 16;
+                for (int v = tid; v < MR * vec_per_row; v += 256) {
+                    const int row = v / vec_per_row, c = v - row * vec_per_row;
+                    *(uint4*)(ldsA + row * pitch + c * 16) = *(const uint4*)(src + (int64_t)row * g.KP + c * 16);
+                }
+            } else {                                          // rows of T * U bytes, four threads each
+                const int row = tid >> 2;
+                const uint8_t* src = g.a + (mt * MR + row) * (int64_t)(g.T * U);
+                for (int tap = tid & 3; tap < g.T; tap += 4)
+                    store_piece<U>(ldsA + row * pitch + tap * U, load_piece<U>(src + tap * U));
             }
         }
         // gather, batch by batch: all entries of a batch are in registers before the rows they name are loaded,

@@ -103,7 +103,7 @@ int launch_igemm_split(const icv_conv_params* p, const Geometry& g, const void* 
     }
     a.stride_bytes = g.in_stride * g.elem_bytes;
     a.a_row_stride = a_mode == A_DENSE_WORKSPACE ? (int64_t)g.T * a.row_bytes : (int64_t)a.stride_bytes;
-    a.a_rows = a_mode == A_DENSE_WORKSPACE ? g.m_tiles * g.MR : g.M;
+    a.a_rows = a_mode == A_DENSE_WORKSPACE ? patch_matrix_rows(g) : g.M;
     a.image_bytes = a_mode == A_GATHERED ? g.image_bytes : 0;
     const int64_t MR = kSplitTileRows[tile], NR = MR;
     const int64_t images = g.per_image ? p->N : 1, img_tiles = (g.img_rows + MR - 1) / MR, n_tiles = (p->K + NR - 1) / NR;

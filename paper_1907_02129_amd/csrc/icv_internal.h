@@ -113,6 +113,24 @@ int64_t tile_span_bound(const icv_conv_params* p, int64_t Hout, int64_t Wout, in
 // Fills g; returns ICV_OK / ICV_ERR_INVALID_ARG / ICV_ERR_UNSUPPORTED.
 int make_geometry(const icv_conv_params* p, Geometry* g);
 
+// The ablation's patch matrix.  Its rows are padded to whole row tiles, but never to more than 64: the any-channel-count and
+// the split-reduction kernels re-read the last row instead of reading past it.  A row is the patch itself, except for the
+// short-row kernel's rows of 8, 16 and 32 bytes, which that kernel copies in whole 32-byte steps (Geometry::KCB).
+inline int64_t patch_matrix_rows(const Geometry& g)
+{
+    const int64_t unit = g.kind == PLAN_MFMA_ANY && g.MR > 64 ? 64 : g.MR;
+    return (g.M + unit - 1) / unit * unit;
+}
+inline bool short_row_words(int dtype, int64_t row_bytes)
+{
+    return dtype != ICV_F32 && (row_bytes == 8 || row_bytes == 16 || row_bytes == 32);
+}
+inline int64_t patch_matrix_row_bytes(const icv_conv_params* p, const Geometry& g)
+{
+    const int64_t row = (int64_t)p->C * g.elem_bytes;
+    return g.kind == PLAN_MFMA_LOWC && short_row_words(p->dtype, row) ? g.KCB : g.T * row;
+}
+
 void set_hip_error(hipError_t e);
 
 #define ICV_HIP_CHECK(expr)                        \

@@ -488,14 +488,14 @@ int launch_im2col(const icv_conv_params* p, const Geometry& g, const void* input
     Im2colArgs a{};      // every field starts at zero; the ones this call uses are set below
     a.in = (const uint8_t*)input;
     a.ws = (uint8_t*)ws;
-    a.M = g.M; a.m_padded = g.m_tiles * g.MR;
+    a.M = g.M; a.m_padded = patch_matrix_rows(g);
     a.Hin = p->Hin; a.Win = p->Win; a.Hout = g.Hout; a.Wout = g.Wout;
     a.S = p->S; a.SY = p->SY; a.SX = p->SX; a.DY = p->DY; a.DX = p->DX; a.PT = p->PT; a.PL = p->PL; a.T = g.T;
     a.CB = p->C * g.elem_bytes;
     a.stride_bytes = (int64_t)g.in_stride * g.elem_bytes;
     const uint32_t zp = p->dtype == ICV_U8I8 ? (uint32_t)p->input_zero_point : 0u;
     a.fill = zp * 0x01010101u;
-    if (g.kind == PLAN_MFMA_LOWC) {
+    if (g.kind == PLAN_MFMA_LOWC && short_row_words(p->dtype, a.CB)) {
         const int64_t threads = a.m_padded * (g.KCB / 8);
         hipLaunchKernelGGL(k_im2col_lowc, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, a, g.KCB);
         ICV_HIP_CHECK(hipGetLastError());

@@ -9,6 +9,7 @@ import torch
 
 from paper_1907_02129_amd import binding as icv
 from paper_1907_02129_amd.workloads import ConvShape, make_tensors
+from test_gpu_parity import check_against_oracle
 
 pytestmark = pytest.mark.gpu
 GATHER = icv.PLAN_GATHER          # a plan whose packed filter the ablation's plain GEMM reads
@@ -41,6 +42,29 @@ def test_static_workspace_variant_matches_the_workspace_variant_twice():
         want, got = _both_ways(s)
         assert torch.equal(want, got), s.name
         assert not torch.equal(got, torch.full_like(got, -9))
+
+
+@pytest.mark.parametrize("s", [
+    # short rows: the patch itself, not padded to whole 32-byte steps (9 bytes, 54 and 36 here)
+    ConvShape("na_short_u8", 4, 372, 370, 1, 8, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="u8i8", zero_point=3, seed=404),
+    ConvShape("na_short_bf16", 2, 380, 379, 3, 8, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=405),
+    ConvShape("na_short_f32", 1, 640, 650, 1, 8, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="f32", seed=406),
+    # few pixels, a long row: rows are padded to 64, not to the tile's 128
+    ConvShape("na_long_row", 1, 8, 8, 4004, 8, 5, 5, PT=2, PL=2, PB=2, PR=2, seed=407),
+    ConvShape("na_rows", 1, 8, 8, 4032, 8, 5, 5, PT=2, PL=2, PB=2, PR=2, seed=408),
+], ids=lambda s: s.name)
+def test_static_workspace_holds_every_patch_matrix_of_its_size(s):
+    """A patch matrix of whole 64-row tiles that fits the buffer is accepted, whichever kernel multiplies it."""
+    x, w = make_tensors(s)
+    buf = icv.prepare(s, icv.to_device(w))
+    esz = {"u8i8": 1, "bf16": 2, "f32": 4}[s.dtype]
+    need = -(-s.N * buf.Hout * buf.Wout // 64) * 64 * s.R * s.S * s.C * esz
+    print("no-alloc", s.name, icv.plan_name(buf.p), need, flush=True)
+    assert need <= icv.static_workspace_bytes() and icv.im2col_bytes(buf.p) <= need
+    buf.output.fill_(-7)
+    icv.conv2d_nhwc_im2col_static(buf.p, icv.to_device(x), buf.packed, buf.output)
+    torch.cuda.synchronize()
+    check_against_oracle(s, buf.output.cpu().numpy(), x, w)
 
 
 def test_static_workspace_variant_rejects_what_does_not_fit():
