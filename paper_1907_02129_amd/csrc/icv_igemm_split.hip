@@ -34,8 +34,14 @@ int choose_split(const icv_conv_params* p, const Geometry& g)
     const bool rows = g.kind == PLAN_MFMA && !g.patch_rows && !g.gemm_on_input;      // goes to the any-channel-count kernel
     double start = 3.7, per_stage;
     if (g.kind == PLAN_MFMA_FREG) {
+        // Not what the kernel takes (16 channels, 3x3: 6.2 us; 32: 8.4; 64: 13 to 15 with one row block per pass, 16 to 18 with two)
+        // but what the split kernel's model below, 1 to 2.4 us short of the truth in fp32, is to be compared with.  Fitted to
+        // 185 drawn problems: of those the split kernel then takes none is slower, and 497 of the 498 us to be gained are.
+        // (3.7 + 0.7 a stage made 14 of them slower: 8 x 9 x 9, 32 to 512 channels, 3x3 8.4 -> 10.6; 4 x 33 x 20, 16 to 480,
+        // stride 2, 6.4 -> 8.1.)
         if (!f32) return -1;
-        per_stage = 0.7;
+        start = g.freg_mb == 1 ? 1.8 : 1.0;
+        per_stage = g.freg_mb == 1 ? 0.64 : 0.8;
     } else if (g.kind == PLAN_MFMA_ANY || rows) {
         start = 2.9;
         per_stage = f32 ? 0.7 : 0.42;

@@ -213,6 +213,22 @@ def test_plan_names_tell_the_kernels_apart(lib):
         assert hooks.family(icv.plan_name(icv.make_params(s))) == "lowc"
 
 
+def test_short_fp32_reductions_stay_with_the_filter_in_registers(lib):
+    """Problems whose split reduction measured slower keep their own kernel; those that gain most are split."""
+    import plan_hooks as hooks
+
+    def fam(n, h, w, C, K, k=3, stride=1, dil=1, plan=0):
+        pad = dil * (k // 2)
+        s = ConvShape("x", n, h, w, C, K, k, k, SY=stride, SX=stride, DY=dil, DX=dil, PT=pad, PL=pad, PB=pad, PR=pad, dtype="f32")
+        return hooks.family(icv.plan_name(icv.make_params(s, plan=plan)))
+
+    for p in ((61, 7, 7, 16, 128), (8, 9, 9, 32, 512), (4, 33, 20, 16, 480, 3, 2), (11, 13, 9, 32, 256, 3, 1, 1, icv.PLAN_PER_IMAGE),
+              (1, 46, 46, 16, 128, 3, 1, 2), (4, 30, 23, 32, 107), (13, 36, 36, 32, 64, 3, 2), (2, 53, 33, 16, 126, 5)):
+        assert fam(*p) == "freg", p
+    for p in ((1, 14, 14, 64, 128), (2, 45, 75, 64, 64), (1, 7, 7, 32, 512), (1, 28, 28, 16, 64, 5)):
+        assert fam(*p) == "split", p
+
+
 def _exact_span(shape, rows):
     """Largest (max - min + 1) over the valid oracle entries of any window of `rows` consecutive output pixels
     that starts at a multiple of `rows` (the library's row tiles)."""
