@@ -295,6 +295,21 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     const bool lowc_ok = plan_kernel == 0 && lowc_shape_supported(p->dtype, row_bytes) &&
                          (!lowc_words || stride_bytes % row_bytes == 0) && T * row_bytes <= 608;
     g->freg_wn = freg_wn; g->freg_mb = freg_mb; g->freg_ring = freg_ring;
+    // The any-channel-count plan.  The batch-independent buffer is laid out for the tile of a batch that fills the chip, and
+    // the kernel runs with the tile this batch wants: 9 x 22 x 30, 320 to 480 channels, 3x3 in bf16, 216 tiles of 128 x 128:
+    // 37.2 us against 43.4 with the layout's tile.
+    g->run_variant = -1;
+    auto to_any_channels = [&]() {
+        g->kind = PLAN_MFMA_ANY;
+        g->variant = choose_any_tile(1, M, p->K, (int32_t)row_bytes, T * row_bytes, p->dtype, plan_per_image);
+        g->MR = kAnyTiles[g->variant].MR;
+        g->NR = kAnyTiles[g->variant].NR;
+        g->run_variant = plan_per_image ? choose_any_tile(p->N, Hout * Wout, p->K, (int32_t)row_bytes, T * row_bytes, p->dtype, false)
+                                        : g->variant;
+        g->KCB = 0; g->ring = 0; g->blocks_per_cu = 0; g->group = 0; g->cc_major = 0;
+        g->stages_per_tap = 1; g->taps_per_stage = 1; g->n_stages = g->T;
+        g->name = kAnyNames[p->dtype][g->run_variant];
+    };
     if (freg_mb) {
         g->kind = PLAN_MFMA_FREG;
         g->variant = -1;
@@ -355,17 +370,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         }
     } else if (plan_kernel != 1 && T * row_bytes < (1ll << 31)) {
         // rows of any other length or alignment
-        g->kind = PLAN_MFMA_ANY;
-        g->variant = choose_any_tile(M, p->K, (int32_t)row_bytes, T * row_bytes, p->dtype, plan_per_image);
-        g->MR = kAnyTiles[g->variant].MR;
-        g->NR = kAnyTiles[g->variant].NR;
-        g->KCB = 0;
-        g->ring = 0;
-        g->blocks_per_cu = 0;
-        g->stages_per_tap = 1;
-        g->taps_per_stage = 1;
-        g->n_stages = g->T;
-        g->name = kAnyNames[p->dtype][g->variant];
+        to_any_channels();
     } else {
         g->kind = PLAN_GENERIC;
         g->variant = -1;
@@ -379,6 +384,14 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         g->n_stages = g->T;
         g->name = kGenericNames[p->dtype];
     }
+    // Rows gathered per kernel element (no pixel range in LDS) go through the any-channel-count kernel, which keeps the filter
+    // out of LDS: 8 x 67 x 67, 224 to 96 channels, 3x3: 49.0 -> 36 us in bf16 and 247.7 -> 178 in fp32; 16 x 40 x 40, 384 to 256: 64.4 -> 58 in
+    // bf16, 44.0 -> 35 in uint8.  The gathering kernel stays for ICV_PLAN_GATHER and, with dense rows, for the plain GEMM.
+    auto gathered_rows = [&]() {
+        return g->kind == PLAN_MFMA && !g->patch_rows && !g->gemm_on_input && plan_kernel == 0 && plan_staging == 0 &&
+               hook_tile != 15 && T * row_bytes < (1ll << 31);
+    };
+    if (plan_per_image && gathered_rows()) to_any_channels();      // first: the split kernel reads that plan's buffers for any N
     // Too little work to fill the chip: the split-reduction kernel.  It reads the buffers of the filter-in-registers and
     // the any-channel-count plans as they are; a problem of the other tensor-core plans, whose filter is laid out for
     // their LDS stages, becomes one of the latter or, with its window in LDS, one of its own -- unless the buffer must serve every batch
@@ -395,7 +408,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
                 window_split_lds_bytes((int)T, row_bytes, span) <= 160 * 1024) {
                 g->name = kWindowSplitNames[p->dtype];
                 g->kind = PLAN_MFMA_WINDOW_SPLIT;
-                g->variant = kAnyTile64;         // what multiplies the patch matrix of the ablation by this filter
+                g->variant = g->run_variant = kAnyTile64;        // what multiplies the patch matrix of the ablation by this filter
                 g->MR = kAnyTiles[kAnyTile64].MR;
                 g->NR = kAnyTiles[kAnyTile64].NR;
                 g->KCB = 0; g->ring = 0; g->blocks_per_cu = 0; g->group = 0; g->cc_major = 0;
@@ -406,7 +419,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         }
         if (g->split_tile >= 0 && g->kind == PLAN_MFMA) {
             g->kind = PLAN_MFMA_ANY;
-            g->variant = kAnySplitTile;
+            g->variant = g->run_variant = kAnySplitTile;
             g->MR = kAnyTiles[kAnySplitTile].MR;
             g->NR = kAnyTiles[kAnySplitTile].NR;
             g->KCB = 0; g->ring = 0; g->blocks_per_cu = 0; g->group = 0;
@@ -415,19 +428,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         }
         if (g->split_tile >= 0) g->name = kSplitNames[p->dtype][g->gemm_on_input][g->split_tile];
     }
-    // Rows gathered per kernel element (no pixel range in LDS) go through the any-channel-count kernel, which keeps the filter
-    // out of LDS: 8 x 67 x 67, 224 to 96 channels, 3x3: 49.0 -> 36 us in bf16 and 247.7 -> 178 in fp32; 16 x 40 x 40, 384 to 256: 64.4 -> 58 in
-    // bf16, 44.0 -> 35 in uint8.  The gathering kernel stays for ICV_PLAN_GATHER and, with dense rows, for the plain GEMM.
-    if (g->kind == PLAN_MFMA && !g->patch_rows && !g->gemm_on_input && plan_kernel == 0 && plan_staging == 0 && hook_tile != 15 &&
-        T * row_bytes < (1ll << 31)) {
-        g->kind = PLAN_MFMA_ANY;
-        g->variant = choose_any_tile(M, p->K, (int32_t)row_bytes, T * row_bytes, p->dtype, plan_per_image);
-        g->MR = kAnyTiles[g->variant].MR;
-        g->NR = kAnyTiles[g->variant].NR;
-        g->KCB = 0; g->ring = 0; g->blocks_per_cu = 0; g->group = 0; g->cc_major = 0;
-        g->stages_per_tap = 1; g->taps_per_stage = 1; g->n_stages = g->T;
-        g->name = kAnyNames[p->dtype][g->variant];
-    }
+    if (gathered_rows()) to_any_channels();
     g->img_rows = g->per_image ? Hout * Wout : M;
     g->img_tiles = (g->img_rows + g->MR - 1) / g->MR;
     g->image_bytes = g->per_image ? (int64_t)p->Hin * p->Win * stride_bytes : 0;

@@ -35,12 +35,13 @@ struct AnyArgs {
     const uint8_t* a;          // input tensor | patch matrix
     const uint8_t* zero_row;
     const uint8_t* w;          // packed filter [32-column block][MFMA step][lane][16 bytes]
-    const int32_t* ind;        // [row tile][kernel element][MR] byte offsets, negative = zero row; null: dense A
+    const int32_t* ind;        // [block][kernel element][block rows] byte offsets, negative = zero row; null: dense A
     void* out;
     int64_t a_row_stride;      // dense A: bytes between rows
     int64_t a_rows;            // dense A: rows that may be read (later ones re-read the last)
     int64_t image_bytes;       // batch-independent buffer: bytes between batch elements of the input (else 0)
     uint32_t img_tiles, img_rows;   // row tiles and output pixels per image (one image = the whole batch otherwise)
+    uint32_t block_shift;      // log2 of the rows of a block of entries, no fewer than a tile's
     FastDiv by_n_tiles, by_img_tiles;
     uint32_t total_tiles, tiles_per_xcd, n_tiles;
     int32_t K, T, out_stride;
@@ -102,7 +103,9 @@ __global__ __launch_bounds__(256, 2) void k_igemm_any(AnyArgs g)
     // ---- A: this thread's piece column and rows
     const int q = tid & 7, r0 = tid >> 3;
     const uint8_t* const a_img = g.a + (int64_t)img * g.image_bytes;
-    const int32_t* const ent = DENSE ? nullptr : g.ind + (int64_t)t_img * g.T * MR + r0;
+    const uint32_t row_img = t_img * MR, blk = row_img >> g.block_shift;
+    // (uniform; a 64-bit address per lane costs the registers that keep four wavefronts of the 128 x 128 tile on a SIMD)
+    const int32_t* const ent = DENSE ? nullptr : g.ind + (((int64_t)blk * g.T) << g.block_shift) + (row_img - (blk << g.block_shift));
     const uint8_t* base[RPT];                    // what the entries count from (dense A: the row)
 #pragma unroll
     for (int i = 0; i < RPT; i++) {
@@ -129,9 +132,9 @@ __global__ __launch_bounds__(256, 2) void k_igemm_any(AnyArgs g)
 #pragma unroll
             for (int i = 0; i < RPT; i++) e[i] = t * g.row_bytes;
         } else {
-            const int32_t* src = ent + (int64_t)t * MR;
+            const uint32_t at = ((uint32_t)t << g.block_shift) + (uint32_t)r0;
 #pragma unroll
-            for (int i = 0; i < RPT; i++) e[i] = src[32 * i];
+            for (int i = 0; i < RPT; i++) e[i] = *(const int32_t*)((const uint8_t*)ent + at * 4u + 128 * i);
         }
         advance();
     };

@@ -48,7 +48,8 @@ int choose_split(const icv_conv_params* p, const Geometry& g)
     } else {
         per_stage = f32 ? 0.61 : (p->dtype == ICV_U8I8 && g.patch_rows ? 0.3 : 0.22);
     }
-    const int64_t own_tiles = images * ((img_rows + g.MR - 1) / g.MR) * ((p->K + g.NR - 1) / g.NR);
+    const int64_t own_mr = g.kind == PLAN_MFMA_ANY ? kAnyTiles[g.run_variant].MR : g.MR, own_nr = g.kind == PLAN_MFMA_ANY ? kAnyTiles[g.run_variant].NR : g.NR;
+    const int64_t own_tiles = images * ((img_rows + own_mr - 1) / own_mr) * ((p->K + own_nr - 1) / own_nr);
     if (own_tiles > cus) {
         // More than one round: in bf16 and uint8 only what measured slow there, tiles of 64 x 64 (two of them share a
         // compute unit at 1.35 times the time of one).  fp32 is bound by the matrix cores, whose work the tile's area counts.

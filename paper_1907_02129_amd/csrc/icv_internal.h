@@ -99,6 +99,9 @@ struct Geometry {
     int32_t cc_major;        // 1: stage = chunk * T + tap (channel chunks outermost), 0: stage = tap * chunks + chunk
     // filter-in-registers plan: column blocks per workgroup (1, 2, 4), row blocks per wavefront and pass, ring rows
     int32_t freg_wn, freg_mb, freg_ring;
+    // any-channel-count plan: the tile the kernel runs with.  MR and NR lay the buffers out; a batch-independent buffer's
+    // must not depend on N, but the kernel reads blocks of MR entries with any tile of no more rows, so this one may
+    int32_t run_variant;
     int32_t split_tile;      // >= 0: tile of the split-reduction kernel, which then runs instead of the plan's own (same buffers)
     const char* name;
     EpilogueArgs ep;         // output stage of this call (plain: no bias, no ReLU, accumulator type)
@@ -166,8 +169,9 @@ size_t patch_lds_bytes(int NR, int KCB, int ring, int cap_units, int ent_copies,
 int launch_igemm_lowc(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                       const int32_t* ind, const void* zero_row, void* out, bool a_direct, hipStream_t s);
 bool lowc_shape_supported(int dtype, int64_t row_bytes);
-// the any-channel-count kernel: tile for a problem (any_batch: independent of the batch size), bytes of its filter
-int choose_any_tile(int64_t M, int32_t K, int32_t row_bytes, int64_t patch_bytes, int32_t dtype, bool any_batch);
+// the any-channel-count kernel: tile for a problem (any_batch: the layout of its buffers, independent of the batch size), bytes
+// of its filter
+int choose_any_tile(int64_t images, int64_t img_rows, int32_t K, int32_t row_bytes, int64_t patch_bytes, int32_t dtype, bool any_batch);
 int64_t any_packed_bytes(const Geometry& g, int32_t row_bytes);
 int launch_igemm_any(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                      const int32_t* ind, const void* zero_row, void* out, int a_mode, hipStream_t s);

@@ -70,6 +70,30 @@ def test_a_row_never_sees_its_neighbours(dtype, C):
     assert np.array_equal(got[~hit], clean[0].cpu().numpy()[~hit])
 
 
+@pytest.mark.parametrize("s,tiles", [
+    # (the number of images decides the tile, the buffers of one image serve all: blocks of 128 entries, tiles of 64 and 128 rows)
+    (ConvShape("one_128x128", 1, 150, 147, 12, 70, 1, 2, seed=635), {1: "64x64", 3: "128x128"}),
+    (ConvShape("one_128x64", 1, 149, 148, 18, 64, 2, 1, dtype="u8i8", zero_point=5, seed=636), {1: "64x64", 3: "128x64"}),
+    (ConvShape("one_rows", 1, 64, 61, 96, 190, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=637), {1: "64x64", 5: "128x64", 14: "128x64"}),
+    (ConvShape("one_f32", 1, 61, 67, 48, 136, 2, 2, dtype="f32", seed=638), {1: "64x64", 14: "128x64"}),
+], ids=lambda v: v.name if hasattr(v, "name") else "")
+def test_one_image_buffer_under_every_tile(s, tiles):
+    x1, w = make_tensors(s)
+    built = icv.prepare(s, icv.to_device(w), plan=icv.PLAN_PER_IMAGE)
+    torch.cuda.synchronize()
+    for n, tile in tiles.items():
+        big = s.with_(N=n)
+        x, _ = make_tensors(big)
+        p = icv.make_params(big, plan=icv.PLAN_PER_IMAGE)
+        print("conv", s.name, n, icv.plan_name(p), flush=True)
+        assert icv.plan_name(p).endswith("any_" + tile), icv.plan_name(p)
+        out = torch.full((n, built.Hout, built.Wout, s.K), -7, dtype=built.output.dtype, device="cuda:0")
+        icv.conv2d_nhwc(p, icv.to_device(x), built.packed, built.indirection, built.zero_row, out)
+        torch.cuda.synchronize()
+        for i in sorted({0, n - 1}):
+            check_against_oracle(s, out[i:i + 1].cpu().numpy(), x[i:i + 1], w)
+
+
 @pytest.mark.parametrize("plan", [0, icv.PLAN_PER_IMAGE, icv.PLAN_GATHER], ids=["auto", "per_image", "gather"])
 @pytest.mark.parametrize("k", [(3, 3), (7, 7), (5, 4)], ids=["3x3", "7x7", "5x4"])
 @pytest.mark.parametrize("dtype,C", [("bf16", 1), ("bf16", 2), ("bf16", 3), ("u8i8", 1), ("u8i8", 2), ("u8i8", 3), ("u8i8", 4),

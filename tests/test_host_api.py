@@ -229,6 +229,22 @@ def test_short_fp32_reductions_stay_with_the_filter_in_registers(lib):
         assert fam(*p) == "split", p
 
 
+@pytest.mark.parametrize("C,K", [(320, 480), (90, 192), (96, 64), (37, 300), (112, 31)])
+def test_batch_independent_layout_serves_the_tile_of_every_batch_size(lib, C, K):
+    """Rows gathered per kernel element: the layout of the one-image buffer and of the filter is the same for every N, the
+    tile the kernel runs with (or the split-reduction kernel in its place) is the one that N wants."""
+    s = ConvShape("x", 1, 22, 30, C, K, 3, 3, PT=1, PL=1, PB=1, PR=1)
+    names, layouts = set(), set()
+    for n in (1, 2, 9, 40, 200):
+        p = icv.make_params(s.with_(N=n), plan=icv.PLAN_PER_IMAGE)
+        names.add(icv.plan_name(p))
+        L = icv.get_indirection_layout(p)
+        layouts.add((L.tile_rows, L.tiles, icv.indirection_bytes(p), icv.packed_filter_bytes(p), icv.zero_row_bytes(p)))
+    assert len(layouts) == 1
+    assert any("split" in n for n in names)
+    assert any(n.endswith("any_128x32" if K <= 32 else ("any_128x128", "any_128x64")) for n in names), names
+
+
 def _exact_span(shape, rows):
     """Largest (max - min + 1) over the valid oracle entries of any window of `rows` consecutive output pixels
     that starts at a multiple of `rows` (the library's row tiles)."""
