@@ -424,10 +424,19 @@ int launch_igemm_lowc(const icv_conv_params* p, const Geometry& g, const void* i
     if (cb_max < 1) return ICV_ERR_UNSUPPORTED;
     if (cb_max > kMaxColBlocks) cb_max = kMaxColBlocks;
     if (cb_max > kb_total) cb_max = kb_total;
-    const int groups = (kb_total + cb_max - 1) / cb_max;
+    int groups = (kb_total + cb_max - 1) / cb_max;
+    const int cus = device_cu_count();
+    const int unit = p->C * g.elem_bytes;
+    // Rows of up to 12 bytes and fewer tiles than compute units: a workgroup takes fewer columns, down to one block, so that more
+    // of the chip works (the rows it gathers again are few).  One 69 x 69 image of three uint8 channels, 256 columns, 3x3
+    // stride 2, fused: 13.6 us with five workgroups of four teams that take all columns, 6.0 with single teams and one
+    // column block each.  Wider rows cost more to gather again (16 bytes: up to 13 % slower so, and 9 % faster).
+    if (unit < 16 && g.m_tiles * groups < cus) {
+        const int64_t fill = cus / g.m_tiles;
+        groups = (int)(fill < kb_total ? (fill > groups ? fill : groups) : kb_total);
+    }
     a.col_blocks = (kb_total + groups - 1) / groups;
     if (groups > 65535) return ICV_ERR_UNSUPPORTED;
-    const int unit = p->C * g.elem_bytes;
     // Teams per workgroup: the path that gathers a whole tile from compact entries in one batch runs several teams
     // on one filter slice (four for the 8-byte rows, two for the wider ones, whose batches need twice the
     // registers), one workgroup per compute unit; every other path runs single teams, two workgroups per compute unit.
@@ -440,9 +449,10 @@ int launch_igemm_lowc(const icv_conv_params* p, const Geometry& g, const void* i
         // teams of one, multiply and move at different times (16 x 224 x 224, 3 channels, 7x7: 51.1 against 56.5 us).
         const int want = p->dtype == ICV_F32 && unit >= 8 ? 1 : (unit <= 8 ? 4 : 2);
         teams = fit >= want ? want : (fit >= 2 ? 2 : 1);
+        // ... and a workgroup of its own for every tile of such rows as long as two per compute unit hold them all
+        if (unit < 16 && g.m_tiles * groups <= 2 * cus) teams = 1;
     }
     const size_t lds_bytes = b_bytes + teams * a_bytes;
-    const int cus = device_cu_count();
     int64_t gx = (int64_t)cus * (teams > 1 ? 1 : 2) / groups;      // workgroups, shared among the column groups
     if (gx < 1) gx = 1;
     if (gx * teams > g.m_tiles) gx = (g.m_tiles + teams - 1) / teams;

@@ -7,9 +7,10 @@ import pytest
 import torch
 
 import plan_hooks as hooks
+from oracle import direct_conv as oracle
 from paper_1907_02129_amd import binding as icv
 from paper_1907_02129_amd.workloads import ConvShape, make_tensors
-from test_gpu_parity import check_against_oracle, run_im2col, run_indirect
+from test_gpu_parity import check_against_oracle, run_fused_case, run_im2col, run_indirect
 
 pytestmark = pytest.mark.gpu
 
@@ -116,6 +117,26 @@ def test_first_layers_of_few_channels(dtype, C, k, plan):
     icv.run(b2, apart)
     torch.cuda.synchronize()
     assert torch.equal(b2.output, buf.output)
+
+
+def _accumulators(s, x, w):
+    return oracle.conv2d_abs(s, x, w) if s.dtype != "u8i8" else (oracle.conv2d_u8i8(s, x, w, s.zero_point), None)
+
+
+@pytest.mark.parametrize("relu,narrow", [(True, True), (False, True), (True, False)], ids=["relu_narrow", "narrow", "relu"])
+@pytest.mark.parametrize("K,hw", [(40, (23, 19)), (300, (23, 19)), (300, (3, 2)), (70, (130, 131))], ids=["k40", "k300", "k300_one_tile", "many_tiles"])
+@pytest.mark.parametrize("dtype,C", [("bf16", 1), ("bf16", 2), ("bf16", 3), ("u8i8", 1), ("u8i8", 2), ("u8i8", 3), ("u8i8", 4),
+                                     ("f32", 1), ("f32", 2), ("f32", 3)])
+def test_first_layers_of_few_channels_with_fused_output(dtype, C, K, hw, relu, narrow):
+    """The output stage of every short row length: one and many column groups of a workgroup, one tile, more tiles than single
+    teams take; padded output pixels, the whole-batch and the one-image buffer."""
+    s = ConvShape(f"first_f_{dtype}_c{C}_k{K}", 2, *hw, C, K, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype=dtype,
+                  zero_point=60 * C if dtype == "u8i8" else 0, seed=660 + C)
+    x, w = make_tensors(s)
+    assert hooks.family(icv.plan_name(icv.make_params(s))) == "lowc"
+    acc, mag = _accumulators(s, x, w)
+    for plan in (0, icv.PLAN_PER_IMAGE):
+        run_fused_case(s, x, w, acc, mag, relu, narrow, plan=plan, out_pixel_stride=K + 3)
 
 
 @pytest.mark.parametrize("plan", [0, icv.PLAN_PER_IMAGE], ids=["auto", "per_image"])
