@@ -117,14 +117,22 @@ __global__ void k_pack_filter_frag(const uint8_t* src, uint8_t* dst, int K, int 
 }
 
 // uint8 tensor-core plans: sums[k] = sum over the R*S*C filter elements of output channel k (the zero-point term of
-// EpilogueArgs).  One wavefront per channel.
+// EpilogueArgs).  One wavefront per channel, 16 bytes from any address a lane: the launch is a serial chain of loads (40
+// channels of 11000 elements, the whole packing: 6.2 us, 19.1 byte by byte).
 __global__ __launch_bounds__(256) void k_filter_channel_sums(const int8_t* filt_krsc, int32_t* sums, int K, int64_t per_channel)
 {
     const int k = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (k >= K) return;
     const int8_t* w = filt_krsc + (int64_t)k * per_channel;
     int32_t acc = 0;
-    for (int64_t i = lane; i < per_channel; i += 64) acc += (int32_t)w[i];
+    const int64_t whole = per_channel / 16;
+    for (int64_t i = lane; i < whole; i += 64) {
+        int v[4];
+        __builtin_memcpy(v, w + 16 * i, 16);
+#pragma unroll
+        for (int j = 0; j < 4; j++) acc = __builtin_amdgcn_sdot4(v[j], 0x01010101, acc, false);
+    }
+    if (lane < (int)(per_channel - 16 * whole)) acc += (int32_t)w[16 * whole + lane];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
     if (lane == 0) sums[k] = acc;

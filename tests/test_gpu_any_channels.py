@@ -119,6 +119,19 @@ def test_first_layers_of_few_channels(dtype, C, k, plan):
     assert torch.equal(b2.output, buf.output)
 
 
+@pytest.mark.parametrize("C,k", [(1, 1), (1, 3), (16, 1), (5, 3), (31, 3), (113, 3), (1024, 1), (1025, 1), (440, 5)])
+def test_filter_sums_behind_the_packed_filter(C, k):
+    """Filters of fewer, as many and more bytes than a lane's 16 and a wavefront's 1024, at any alignment, extreme weights."""
+    s = ConvShape(f"sums_{C}_{k}", 1, 8, 8, C, 37, k, k, dtype="u8i8", zero_point=3, seed=645)
+    _, w = make_tensors(s)
+    w[0], w[1] = -128, 127
+    p = icv.make_params(s)
+    packed = torch.zeros(icv.packed_filter_bytes(p), dtype=torch.uint8, device="cuda:0")
+    icv.pack_filter(p, icv.to_device(w), packed)
+    sums = packed[-((s.K * 4 + 15) // 16 * 16):].cpu().numpy().view(np.int32)[:s.K]
+    assert np.array_equal(sums, w.astype(np.int64).reshape(s.K, -1).sum(axis=1))
+
+
 def _accumulators(s, x, w):
     return oracle.conv2d_abs(s, x, w) if s.dtype != "u8i8" else (oracle.conv2d_u8i8(s, x, w, s.zero_point), None)
 
