@@ -1,4 +1,5 @@
-// Vector-ALU indirect GEMM: any shape, any type, on request (ICV_PLAN_VECTOR_ALU).
+// Vector-ALU indirect GEMM: any shape, any type, on request (ICV_PLAN_VECTOR_ALU) and for patches of 2 GiB and more, which
+// the other kernels' 32-bit offsets do not reach.
 //
 // It is Listing 3 with one output element per thread: for each kernel element load the row pointer from
 // the indirection buffer (entry = byte offset from the input base; < 0 -> the zero row), take the C-long dot product with the filter row,

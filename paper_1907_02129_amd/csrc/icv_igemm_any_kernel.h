@@ -54,25 +54,11 @@ struct AnyArgs {
     EpilogueArgs ep;
 };
 
-typedef uint32_t any_u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ inline any_u32x4 load16_any(const uint8_t* p)      // 16 bytes from any address
+__device__ inline bytes16_t load16_any(const uint8_t* p)      // 16 bytes from any address
 {
-    any_u32x4 v;
+    bytes16_t v;
     __builtin_memcpy(&v, p, 16);
     return v;
-}
-
-// v >> (8 * bytes) as a 128-bit number, bytes uniform, 0..15
-__device__ inline any_u32x4 shift_down(any_u32x4 v, int bytes)
-{
-    const int words = bytes >> 2;
-    if (words == 1) v = any_u32x4{v.y, v.z, v.w, 0u};
-    else if (words == 2) v = any_u32x4{v.z, v.w, 0u, 0u};
-    else if (words == 3) v = any_u32x4{v.w, 0u, 0u, 0u};
-    const uint32_t b = (uint32_t)bytes & 3u;
-    return any_u32x4{__builtin_amdgcn_alignbyte(v.y, v.x, b), __builtin_amdgcn_alignbyte(v.z, v.y, b),
-                     __builtin_amdgcn_alignbyte(v.w, v.z, b), __builtin_amdgcn_alignbyte(0u, v.w, b)};
 }
 
 // length of a pixel row: whole pieces; a padded last piece; shorter than a piece
@@ -138,7 +124,7 @@ __global__ __launch_bounds__(256, 2) void k_igemm_any(AnyArgs g)
         }
         advance();
     };
-    any_u32x4 av[RPT];
+    bytes16_t av[RPT];
     bool v_past = false, v_last = false;         // the pieces in av lie past the patch; are the last of their row
     auto read_rows = [&]() {
         v_past = e_tap >= g.T;
@@ -150,7 +136,7 @@ __global__ __launch_bounds__(256, 2) void k_igemm_any(AnyArgs g)
             const uint8_t* src = e[i] < 0 ? g.zero_row : base[i] + (uint32_t)e[i];
             if constexpr (TAIL == ROWS_SHORT) {
                 // byte by byte: nothing beyond the row may be read
-                any_u32x4 v = {0u, 0u, 0u, 0u};
+                bytes16_t v = {0u, 0u, 0u, 0u};
 #pragma unroll
                 for (int b = 0; b < 15; b++) {
                     const uint32_t x = src[b < g.row_bytes ? b : 0];
@@ -166,13 +152,13 @@ __global__ __launch_bounds__(256, 2) void k_igemm_any(AnyArgs g)
         uint8_t* d = lds + buf * (MR * PITCH) + r0 * PITCH + q * 16;
 #pragma unroll
         for (int i = 0; i < RPT; i++) {
-            any_u32x4 v = av[i];
+            bytes16_t v = av[i];
             if constexpr (TAIL == ROWS_TAIL) {
-                const any_u32x4 s = shift_down(v, g.tail_shift);
+                const bytes16_t s = shift_down(v, g.tail_shift);
                 v = v_last ? s : v;
             }
-            if (v_past) v = any_u32x4{0u, 0u, 0u, 0u};
-            *(any_u32x4*)(d + i * 32 * PITCH) = v;
+            if (v_past) v = bytes16_t{0u, 0u, 0u, 0u};
+            *(bytes16_t*)(d + i * 32 * PITCH) = v;
         }
     };
 

@@ -1,5 +1,5 @@
-// Tensor-core Indirect GEMM for very few input channels (first-layer convolutions: C*sizeof(element) of
-// 8, 16 or 32 bytes per pixel row).
+// Tensor-core Indirect GEMM for very few input channels (first-layer convolutions): pixel rows of 8, 16 or 32 bytes, of one
+// to three bf16, one to four uint8 or one to three fp32 channels.
 //
 // With so short rows one kernel element is less than an MFMA k-step, so the two nested loops of Listing 3
 // (kernel elements outside, channels inside) are flattened: the reduction index is k = tap*C + c, the whole
@@ -375,11 +375,15 @@ static int launch_lowc(const LowcArgs& a, dim3 grid, size_t lds_bytes, bool plai
 template <int DT, int U>
 static int launch_lowc_teams(const LowcArgs& a, dim3 grid, int teams, size_t lds_bytes, bool plain, hipStream_t s)
 {
-    if (teams == 4) {
-        if constexpr (U <= 8) return launch_lowc<DT, U, 4>(a, grid, lds_bytes, plain, s);      // wider rows: two at most
-        return ICV_ERR_UNSUPPORTED;
+    if constexpr (DT == ICV_F32 && U >= 8) {                  // always one (launch_igemm_lowc says why)
+        return teams == 1 ? launch_lowc<DT, U, 1>(a, grid, lds_bytes, plain, s) : ICV_ERR_UNSUPPORTED;
+    } else {
+        if (teams == 4) {
+            if constexpr (U <= 8) return launch_lowc<DT, U, 4>(a, grid, lds_bytes, plain, s);      // wider rows: two at most
+            return ICV_ERR_UNSUPPORTED;
+        }
+        return teams == 2 ? launch_lowc<DT, U, 2>(a, grid, lds_bytes, plain, s) : launch_lowc<DT, U, 1>(a, grid, lds_bytes, plain, s);
     }
-    return teams == 2 ? launch_lowc<DT, U, 2>(a, grid, lds_bytes, plain, s) : launch_lowc<DT, U, 1>(a, grid, lds_bytes, plain, s);
 }
 
 // rows the kernel is built for, by type

@@ -53,20 +53,7 @@ struct SplitArgs {
 
 enum SplitRows : int { SPLIT_DENSE = 0, SPLIT_INT32 = 1, SPLIT_BLOCK16 = 2 };
 
-typedef uint32_t split_u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-
-// v >> (8 * bytes) as a 128-bit number, bytes uniform, 0..15
-__device__ inline split_u32x4 split_shift_down(split_u32x4 v, int bytes)
-{
-    const int words = bytes >> 2;
-    if (words == 1) v = split_u32x4{v.y, v.z, v.w, 0u};
-    else if (words == 2) v = split_u32x4{v.z, v.w, 0u, 0u};
-    else if (words == 3) v = split_u32x4{v.w, 0u, 0u, 0u};
-    const uint32_t b = (uint32_t)bytes & 3u;
-    return split_u32x4{__builtin_amdgcn_alignbyte(v.y, v.x, b), __builtin_amdgcn_alignbyte(v.z, v.y, b),
-                       __builtin_amdgcn_alignbyte(v.w, v.z, b), __builtin_amdgcn_alignbyte(0u, v.w, b)};
-}
 
 template <int DT, int BLK>
 struct SplitAcc {
@@ -175,7 +162,7 @@ __global__ __launch_bounds__(64 * kSplitMaxSlices) void k_igemm_split(SplitArgs 
         piece += g.step_pieces;
         if (piece >= g.P) { piece -= g.P; ++tap; }
     };
-    split_u32x4 av[D][RPT];
+    bytes16_t av[D][RPT];
     bool v_past[D], v_last[D];
     auto read_rows = [&](int d, bool used) __attribute__((always_inline)) {
         v_past[d] = e_off[d] < 0;
@@ -199,13 +186,13 @@ __global__ __launch_bounds__(64 * kSplitMaxSlices) void k_igemm_split(SplitArgs 
     auto to_lds = [&](int d) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < RPT; i++) {
-            split_u32x4 v = av[d][i];
+            bytes16_t v = av[d][i];
             if constexpr (TAIL) {
-                const split_u32x4 s = split_shift_down(v, g.tail_shift);
+                const bytes16_t s = shift_down(v, g.tail_shift);
                 v = v_last[d] ? s : v;
             }
-            if (v_past[d]) v = split_u32x4{0u, 0u, 0u, 0u};
-            *(split_u32x4*)(mine + (r0 + 8 * i) * kSplitPitch + q * 16) = v;
+            if (v_past[d]) v = bytes16_t{0u, 0u, 0u, 0u};
+            *(bytes16_t*)(mine + (r0 + 8 * i) * kSplitPitch + q * 16) = v;
         }
     };
 
@@ -282,7 +269,7 @@ __global__ __launch_bounds__(64 * kSplitMaxSlices) void k_igemm_split(SplitArgs 
     const int64_t row0 = (int64_t)img * g.img_rows + (int64_t)t_img * BLK;
     const int64_t m_end = (int64_t)(img + 1) * g.img_rows;
     const int threads = g.slices * 64;
-    typedef out_acc_t out4_t __attribute__((ext_vector_type(4)));
+    typedef typename FourOutputs<I8>::vec_t out4_t;
     {
         out_acc_t* part = (out_acc_t*)mine;      // [BLK][BLK]
         asm volatile("" ::: "memory");
@@ -299,32 +286,7 @@ __global__ __launch_bounds__(64 * kSplitMaxSlices) void k_igemm_split(SplitArgs 
             const int64_t row = row0 + v / (BLK / 4);
             const int32_t col = (int32_t)nt * BLK + v % (BLK / 4) * 4;
             if (row >= m_end) continue;
-            const int64_t at = row * g.out_stride + col;
-#pragma unroll
-            for (int u = 0; u < 4; u++) sum[u] += output_bias<out_acc_t>(g.ep, col + u, g.K);
-            if (g.vector_out && col + 4 <= g.K) {
-#pragma unroll
-                for (int u = 0; u < 4; u++)
-                    if (g.ep.relu) sum[u] = sum[u] > (out_acc_t)0 ? sum[u] : (out_acc_t)0;
-                if (g.ep.out_kind == ICV_OUT_ACC) {
-                    *(out4_t*)((out_acc_t*)g.out + at) = sum;
-                } else if constexpr (I8) {
-                    uint8_t c[4];
-#pragma unroll
-                    for (int u = 0; u < 4; u++) emit_output(c, u, (int32_t)sum[u], g.ep);
-                    *(uint32_t*)((uint8_t*)g.out + at) = (uint32_t)c[0] | (uint32_t)c[1] << 8 | (uint32_t)c[2] << 16 | (uint32_t)c[3] << 24;
-                } else {
-                    typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
-                    bf16x4_t c;
-#pragma unroll
-                    for (int u = 0; u < 4; u++) c[u] = (__bf16)sum[u];
-                    *(bf16x4_t*)((__bf16*)g.out + at) = c;
-                }
-            } else {
-#pragma unroll
-                for (int u = 0; u < 4; u++)
-                    if (col + u < g.K) emit_output(g.out, at + u, (out_acc_t)sum[u], g.ep);
-            }
+            store_four<I8>(g.out, row * g.out_stride + col, sum, col, g.K, g.vector_out, g.ep);
         }
     }
 }

@@ -153,7 +153,7 @@ __global__ __launch_bounds__(64 * kWindowWaves) void k_igemm_window_split(Window
     }
 
     // ---- sum the partial tiles, 32 rows at a time, in the window's place
-    typedef out_acc_t out4_t __attribute__((ext_vector_type(4)));
+    typedef typename FourOutputs<I8>::vec_t out4_t;
 #pragma unroll
     for (int i = 0; i < 2; i++) {
         __syncthreads();                         // the window has been read; the sums of the rows before have been taken
@@ -169,34 +169,7 @@ __global__ __launch_bounds__(64 * kWindowWaves) void k_igemm_window_split(Window
         for (int w = 1; w < kWindowWaves; w++) sum += *(const out4_t*)(lds + w * 8192 + v * 16);
         const int64_t row = (int64_t)mt * 64 + i * 32 + (v >> 4);
         const int32_t col = (int32_t)nt * 64 + (v & 15) * 4;
-        if (row < (int64_t)g.M) {
-            const int64_t o = row * g.out_stride + col;
-#pragma unroll
-            for (int u = 0; u < 4; u++) sum[u] += output_bias<out_acc_t>(g.ep, col + u, g.K);
-            if (g.vector_out && col + 4 <= g.K) {
-#pragma unroll
-                for (int u = 0; u < 4; u++)
-                    if (g.ep.relu) sum[u] = sum[u] > (out_acc_t)0 ? sum[u] : (out_acc_t)0;
-                if (g.ep.out_kind == ICV_OUT_ACC) {
-                    *(out4_t*)((out_acc_t*)g.out + o) = sum;
-                } else if constexpr (I8) {
-                    uint8_t c[4];
-#pragma unroll
-                    for (int u = 0; u < 4; u++) emit_output(c, u, (int32_t)sum[u], g.ep);
-                    *(uint32_t*)((uint8_t*)g.out + o) = (uint32_t)c[0] | (uint32_t)c[1] << 8 | (uint32_t)c[2] << 16 | (uint32_t)c[3] << 24;
-                } else {
-                    typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
-                    bf16x4_t c;
-#pragma unroll
-                    for (int u = 0; u < 4; u++) c[u] = (__bf16)sum[u];
-                    *(bf16x4_t*)((__bf16*)g.out + o) = c;
-                }
-            } else {
-#pragma unroll
-                for (int u = 0; u < 4; u++)
-                    if (col + u < g.K) emit_output(g.out, o + u, (out_acc_t)sum[u], g.ep);
-            }
-        }
+        if (row < (int64_t)g.M) store_four<I8>(g.out, row * g.out_stride + col, sum, col, g.K, g.vector_out, g.ep);
     }
 }
 

@@ -10,7 +10,7 @@ namespace icv {
 // Which inner kernel serves a problem.
 enum PlanKind : int32_t {
     PLAN_INVALID = 0,
-    PLAN_GENERIC = 1,   // vector-ALU kernel, any C, any dtype (on request)
+    PLAN_GENERIC = 1,   // vector-ALU kernel, any C, any dtype (on request; patches of 2 GiB and more)
     PLAN_MFMA = 2,      // tensor-core indirect GEMM, C a multiple of the k-granule
     PLAN_MFMA_LOWC = 3, // tensor-core indirect GEMM for short pixel rows (first-layer convolutions)
     PLAN_MFMA_FREG = 4, // tensor-core indirect GEMM with the filter in registers and the input window in an LDS ring

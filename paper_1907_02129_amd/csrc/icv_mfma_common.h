@@ -168,6 +168,59 @@ __device__ inline void store_tile(void* out, const ACC (&acc)[MB][NB], int64_t M
     }
 }
 
+// v >> (8 * bytes) as a 128-bit number, bytes uniform, 0..15
+typedef uint32_t bytes16_t __attribute__((ext_vector_type(4)));
+__device__ inline bytes16_t shift_down(bytes16_t v, int bytes)
+{
+    const int words = bytes >> 2;
+    if (words == 1) v = bytes16_t{v.y, v.z, v.w, 0u};
+    else if (words == 2) v = bytes16_t{v.z, v.w, 0u, 0u};
+    else if (words == 3) v = bytes16_t{v.w, 0u, 0u, 0u};
+    const uint32_t b = (uint32_t)bytes & 3u;
+    return bytes16_t{__builtin_amdgcn_alignbyte(v.y, v.x, b), __builtin_amdgcn_alignbyte(v.z, v.y, b),
+                     __builtin_amdgcn_alignbyte(v.w, v.z, b), __builtin_amdgcn_alignbyte(0u, v.w, b)};
+}
+
+// Output stage of the split-reduction kernels: the accumulators of columns col .. col + 3 of one output pixel, the first at
+// element `at`.  vector_out (pixel stride a multiple of four): one store for four columns inside K.
+template <bool I8>
+struct FourOutputs {
+    typedef typename std::conditional<I8, int32_t, float>::type acc_t;
+    typedef acc_t vec_t __attribute__((ext_vector_type(4)));
+};
+template <bool I8>
+__device__ inline void store_four(void* out, int64_t at, typename FourOutputs<I8>::vec_t sum, int32_t col, int32_t K, int32_t vector_out,
+                                  const EpilogueArgs& ep)
+{
+    using out_acc_t = typename FourOutputs<I8>::acc_t;
+    typedef typename FourOutputs<I8>::vec_t out4_t;
+#pragma unroll
+    for (int u = 0; u < 4; u++) sum[u] += output_bias<out_acc_t>(ep, col + u, K);
+    if (vector_out && col + 4 <= K) {
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            if (ep.relu) sum[u] = sum[u] > (out_acc_t)0 ? sum[u] : (out_acc_t)0;
+        if (ep.out_kind == ICV_OUT_ACC) {
+            *(out4_t*)((out_acc_t*)out + at) = sum;
+        } else if constexpr (I8) {
+            uint8_t c[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) emit_output(c, u, (int32_t)sum[u], ep);
+            *(uint32_t*)((uint8_t*)out + at) = (uint32_t)c[0] | (uint32_t)c[1] << 8 | (uint32_t)c[2] << 16 | (uint32_t)c[3] << 24;
+        } else {
+            typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+            bf16x4_t c;
+#pragma unroll
+            for (int u = 0; u < 4; u++) c[u] = (__bf16)sum[u];
+            *(bf16x4_t*)((__bf16*)out + at) = c;
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            if (col + u < K) emit_output(out, at + u, (out_acc_t)sum[u], ep);
+    }
+}
+
 // Tile list of a persistent workgroup.  Workgroups are dealt round-robin to the 8 XCDs (block b runs on
 // XCD b % 8).  In XCD mode XCD x owns the contiguous tile range [first, first + count) and its G/8 workgroups
 // take tiles first + i, first + i + G/8, ... ; otherwise block b takes b, b + G, ...
