@@ -152,15 +152,55 @@ def test_first_layers_of_few_channels_with_fused_output(dtype, C, K, hw, relu, n
         run_fused_case(s, x, w, acc, mag, relu, narrow, plan=plan, out_pixel_stride=K + 3)
 
 
+_FUSED = [
+    # (shape, tile): every tile with whole rows and with a padded last piece, rows shorter than a piece, dense rows
+    (ConvShape("fu_128x128_whole", 3, 150, 147, 24, 70, 1, 2, seed=681), "any_128x128"),
+    (ConvShape("fu_128x128_tail", 3, 150, 147, 12, 70, 1, 2, seed=682), "any_128x128"),
+    (ConvShape("fu_128x64_whole", 3, 149, 148, 48, 64, 2, 1, dtype="u8i8", zero_point=128, seed=683), "any_128x64"),
+    (ConvShape("fu_128x64_tail", 3, 149, 148, 18, 64, 2, 1, dtype="u8i8", zero_point=5, seed=684), "any_128x64"),
+    (ConvShape("fu_64x64_whole", 2, 13, 11, 48, 192, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=685), "any_64x64"),
+    (ConvShape("fu_64x64_tail", 2, 13, 11, 37, 130, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=686), "any_64x64"),
+    (ConvShape("fu_128x32_whole", 2, 13, 11, 40, 24, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=687), "any_128x32"),
+    (ConvShape("fu_128x32_tail", 2, 13, 11, 37, 8, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=688), "any_128x32"),
+    (ConvShape("fu_short", 2, 13, 11, 5, 16, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="u8i8", zero_point=99, seed=689), "any_64x64"),
+    (ConvShape("fu_1x1", 3, 9, 7, 40, 72, 1, 1, seed=690), "any_64x64"),
+    (ConvShape("fu_1x1_u8", 2, 17, 5, 33, 48, 1, 1, dtype="u8i8", zero_point=200, seed=691), "any_64x64"),
+    (ConvShape("fu_f32_64x64", 2, 13, 11, 33, 140, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="f32", seed=692), "any_64x64"),
+    (ConvShape("fu_f32_128x32", 2, 13, 11, 5, 31, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="f32", seed=693), "any_128x32"),
+]
+
+
+@pytest.mark.parametrize("relu,narrow", [(True, True), (False, True), (True, False), (False, False)],
+                         ids=["relu_narrow", "narrow", "relu", "bias"])
+@pytest.mark.parametrize("s,tile", _FUSED, ids=lambda v: getattr(v, "name", ""))
+def test_fused_output_of_every_tile(s, tile, relu, narrow):
+    """Bias, ReLU and narrow output of the any-channel-count kernel itself (never the split-reduction kernel in its place), padded
+    output pixels, with the whole-batch and the one-image buffer."""
+    x, w = make_tensors(s)
+    acc, mag = _accumulators(s, x, w)
+    for plan in (hooks.NO_SPLIT, hooks.NO_SPLIT | icv.PLAN_PER_IMAGE):
+        assert icv.plan_name(icv.make_params(s, plan=plan)).endswith(tile)
+        run_fused_case(s, x, w, acc, mag, relu, narrow, plan=plan, out_pixel_stride=s.K + 5)
+
+
 @pytest.mark.parametrize("plan", [0, icv.PLAN_PER_IMAGE], ids=["auto", "per_image"])
 @pytest.mark.parametrize("dtype,C,K", [("bf16", 96, 140), ("bf16", 96, 64), ("bf16", 160, 24), ("u8i8", 192, 70), ("f32", 48, 33)])
 def test_aligned_rows_that_are_gathered_per_kernel_element(dtype, C, K, plan):
-    """Rows of whole 64-byte units that no power of two fits take the same kernel: every tile, two strides, pixels apart."""
+    """Rows of whole 64-byte units that no power of two fits take the same kernel (and few output pixels the split-reduction
+    kernel), checked on several images of a large batch too, where the larger tiles run."""
     s = ConvShape(f"rows_{dtype}_{C}", 5, 45, 47, C, K, 3, 3, SY=1 + (K == 24), PT=1, PL=1, PB=1, PR=1, dtype=dtype,
                   zero_point=11 if dtype == "u8i8" else 0, seed=670)
     name = icv.plan_name(icv.make_params(s, plan=plan))
     print("conv", s.name, name, flush=True)
-    assert hooks.family(name) in ("any", "split")
+    assert name.endswith("split_32x32" if C == 160 else "any_64x64"), name
+    big = s.with_(N=40)
+    tile = {("bf16", 96): "128x64", ("bf16", 160): "128x32", ("u8i8", 192): "128x128", ("f32", 48): "128x64"}[dtype, C]
+    assert icv.plan_name(icv.make_params(big, plan=plan)).endswith("any_" + tile)
+    xb, wb = make_tensors(big)
+    bbuf, _ = run_indirect(big, xb, wb, plan=plan)
+    one = s.with_(N=1)
+    for n in (0, 17, 39):
+        check_against_oracle(one, bbuf.output[n:n + 1].cpu().numpy(), xb[n:n + 1], wb)
     x, w = make_tensors(s)
     buf, xd = run_indirect(s, x, w, plan=plan)
     check_against_oracle(s, buf.output.cpu().numpy(), x, w)

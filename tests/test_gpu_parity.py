@@ -205,7 +205,7 @@ def _small_shapes():
     out.append(ConvShape("s_i8_c8_5x5_k300", 1, 11, 23, 8, 300, 5, 5, PT=2, PL=2, PB=1, PR=1, dtype="u8i8", zero_point=128, seed=40))
     out.append(ConvShape("s_bf16_c16_3x3_k96", 2, 13, 9, 16, 96, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=45))
     out.append(ConvShape("s_bf16_c16_1x1_k33", 2, 13, 9, 16, 33, 1, 1, seed=46))
-    # vector-ALU fallback: odd channel counts; and a zero point other than 128 (tensor cores: the filter-sum term)
+    # odd channel counts; and a zero point other than 128 (tensor cores: the filter-sum term)
     out.append(ConvShape("s_f32_odd", 2, 9, 10, 5, 7, 3, 3, SY=2, SX=1, PT=1, PL=2, PB=0, PR=1, dtype="f32", dist="uniform", seed=41))
     out.append(ConvShape("s_bf16_c3", 1, 12, 12, 3, 70, 7, 7, SY=2, SX=2, PT=3, PL=3, PB=3, PR=3, seed=42))
     out.append(ConvShape("s_i8_zp7", 1, 9, 9, 64, 16, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="u8i8", zero_point=7, seed=43))
@@ -249,13 +249,16 @@ def _random_tensor_core_shapes(n=36):
     return out
 
 
+@pytest.mark.parametrize("plan", [0, hooks.NO_SPLIT], ids=["auto", "own_kernel"])
 @pytest.mark.parametrize("s", _random_tensor_core_shapes(), ids=lambda s: s.name)
-def test_random_tensor_core_shapes_match_oracle(s):
-    name = icv.plan_name(icv.make_params(s))
+def test_random_tensor_core_shapes_match_oracle(s, plan):
+    """The library's choice (at these sizes mostly the split-reduction kernel) and the kernel it takes the problem from; how
+    many shapes each kernel gets is asserted in test_host_api.py."""
+    name = icv.plan_name(icv.make_params(s, plan=plan))
     _say("conv", s.name, name, s)
-    assert name.startswith(("mfma_", "gemm_"))
+    assert hooks.family(name) in (("patch", "gather", "freg") if plan else ("split", "any", "freg")), name
     x, w = make_tensors(s)
-    buf, xd = run_indirect(s, x, w)
+    buf, xd = run_indirect(s, x, w, plan=plan)
     check_against_oracle(s, buf.output.cpu().numpy(), x, w)
 
 
@@ -574,9 +577,11 @@ def test_fp32_pointwise_convolution_and_ablation_on_the_matrix_cores():
     """1x1 stride-1 in fp32 runs as the plain GEMM on the input; the im2col + GEMM comparison path runs in fp32 too."""
     s = ConvShape("f_1x1", 3, 7, 11, 64, 72, 1, 1, dtype="f32", seed=411)
     x, w = make_tensors(s)
-    assert icv.plan_name(icv.make_params(s)).startswith("gemm_f32")
-    buf, xd = run_indirect(s, x, w)
-    check_against_oracle(s, buf.output.cpu().numpy(), x, w)
+    for plan in (0, hooks.NO_SPLIT):
+        assert icv.plan_name(icv.make_params(s, plan=plan)).startswith("gemm_f32")
+        buf, xd = run_indirect(s, x, w, plan=plan)
+        check_against_oracle(s, buf.output.cpu().numpy(), x, w)
+    assert hooks.family(icv.plan_name(buf.p)) == "gemm"
     s = _f32_mfma_shapes()[0]
     x, w = make_tensors(s)
     buf = icv.prepare(s, icv.to_device(w), plan=icv.PLAN_GATHER)
@@ -614,9 +619,12 @@ def test_pointwise_convolution_runs_as_gemm_on_the_input(s, pixel_stride):
         v = flat.reshape(-1, pixel_stride)
         v[:, :s.C] = x.reshape(-1, s.C)
         xp = flat
-    for plan in (0, icv.PLAN_GATHER):                           # dispatch to the GEMM, and the gathered path for comparison
+    # the library's choice, the plain GEMM kernel, dense rows through the split kernel, the gathered path
+    for plan in (0, hooks.NO_SPLIT, hooks.tile(8), icv.PLAN_GATHER):
         p = icv.make_params(s, plan, in_pixel_stride=pixel_stride)
-        assert icv.plan_name(p).startswith("gemm_" if plan == 0 else "mfma_"), icv.plan_name(p)
+        assert icv.plan_name(p).startswith("mfma_" if plan == icv.PLAN_GATHER else "gemm_"), icv.plan_name(p)
+        assert hooks.family(icv.plan_name(p)) in {0: ("gemm", "split"), hooks.NO_SPLIT: ("gemm",), hooks.tile(8): ("split",),
+                                                  icv.PLAN_GATHER: ("gather",)}[plan]
         _say("pointwise", s.name, icv.plan_name(p), "pixel stride", pixel_stride)
         buf = icv.prepare(s, icv.to_device(w), plan=plan, in_pixel_stride=pixel_stride)
         buf.output.fill_(-7)
@@ -632,7 +640,7 @@ def test_pointwise_convolution_runs_as_gemm_on_the_input(s, pixel_stride):
 PER_IMAGE = icv.PLAN_PER_IMAGE
 
 PER_IMAGE_SHAPES = [
-    CONFIGS["cfg1_tiny_f32"].with_(N=3),                                                            # vector ALU
+    CONFIGS["cfg1_tiny_f32"].with_(N=3),
     ConvShape("b_patch", 3, 19, 23, 64, 96, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=101),                # 437 pixels per image
     ConvShape("b_patch_chunks", 2, 13, 17, 128, 72, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=102),
     ConvShape("b_gather", 4, 13, 17, 96, 40, 3, 3, SY=2, SX=1, PT=1, PL=1, PB=1, PR=1, seed=103),   # rows per element
@@ -654,19 +662,23 @@ PER_IMAGE_SHAPES = [
 ]
 
 
+@pytest.mark.parametrize("algo", [0, hooks.NO_SPLIT, icv.PLAN_VECTOR_ALU], ids=["auto", "own_kernel", "vector_alu"])
 @pytest.mark.parametrize("s", PER_IMAGE_SHAPES, ids=lambda s: s.name)
-def test_batch_independent_buffer_matches_oracle(s):
+def test_batch_independent_buffer_matches_oracle(s, algo):
+    plan = PER_IMAGE | algo
     x, w = make_tensors(s)
-    name = icv.plan_name(icv.make_params(s, plan=PER_IMAGE))
+    name = icv.plan_name(icv.make_params(s, plan=plan))
     _say("per-image", s.name, name)
-    buf, xd = run_indirect(s, x, w, plan=PER_IMAGE)
+    assert "split" not in name or not algo
+    assert (hooks.family(name) == "vector_alu") == (algo == icv.PLAN_VECTOR_ALU)
+    buf, xd = run_indirect(s, x, w, plan=plan)
     check_against_oracle(s, buf.output.cpu().numpy(), x, w)
     # the buffer is that of one image: entry by entry the oracle's entries of batch element 0
     one = s.with_(N=1)
-    built = icv.prepare(one, icv.to_device(w), plan=PER_IMAGE)
+    built = icv.prepare(one, icv.to_device(w), plan=plan)
     got, pad = layout.logical_indirection(built.p, built.indirection, built.M)
     assert np.array_equal(got, oracle.indirection(one)) and np.all(pad == -1)
-    assert icv.indirection_bytes(buf.p) == icv.indirection_bytes(icv.make_params(one, plan=PER_IMAGE))
+    assert icv.indirection_bytes(buf.p) == icv.indirection_bytes(icv.make_params(one, plan=plan))
 
 
 def test_batch_independent_buffer_serves_any_batch_size():
@@ -696,14 +708,15 @@ MODEL_LAYERS = resnet18_layers(2) + squeezenet10_layers(2)
 def test_model_layers_match_oracle(s):
     """Every distinct convolution of ResNet-18 and SqueezeNet 1.0 (section 3.1, Table 2) at batch 2, with the plan
     the library picks and with the batch-independent buffer.  Channel counts that are no whole 64-byte rows (3; 48) run
-    twice: stored padded with zeros, as the benchmark's sweep keeps them, and as they are."""
+    twice: stored padded with zeros, as the benchmark's sweep keeps them, and as they are (on the vector ALUs too)."""
     stored = icv.stored_for_tensor_cores(s)
     for sh in ([stored, s] if stored is not s else [s]):
         x, w = make_tensors(sh)
-        for plan in (0, PER_IMAGE):
+        for plan in (0, PER_IMAGE) if sh is stored else (0, PER_IMAGE, icv.PLAN_VECTOR_ALU):
             name = icv.plan_name(icv.make_params(sh, plan=plan))
             _say("layer", sh.name, "C", sh.C, name)
-            assert sh is stored or hooks.family(name) in ("lowc", "any", "split"), name
+            if sh is not stored:
+                assert hooks.family(name) in (("vector_alu",) if plan == icv.PLAN_VECTOR_ALU else ("lowc", "any")), name
             buf, xd = run_indirect(sh, x, w, plan=plan)
             check_against_oracle(sh, buf.output.cpu().numpy(), x, w)
 
@@ -761,23 +774,29 @@ def test_one_zero_row_shared_by_operators_of_different_width():
 
 
 # ---------------------------------------------------------------- launches captured into a HIP graph
-@pytest.mark.parametrize("s", [
-    ConvShape("h_regs", 3, 19, 23, 64, 96, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=121),
-    ConvShape("h_patch", 3, 19, 23, 256, 96, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=126),
-    ConvShape("h_gather", 2, 13, 17, 96, 40, 3, 3, SY=2, SX=1, PT=1, PL=1, PB=1, PR=1, seed=122),
-    ConvShape("h_lowc", 2, 30, 26, 4, 70, 7, 7, SY=2, SX=2, PT=3, PL=3, PB=3, PR=3, seed=123),
-    ConvShape("h_gemm", 2, 21, 13, 256, 64, 1, 1, seed=124),
-    ConvShape("h_i8", 2, 15, 15, 256, 80, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="u8i8", zero_point=64, seed=125),
-], ids=lambda s: s.name)
-def test_graph_replays_match_eager(s):
+_H_PATCH = ConvShape("h_patch", 3, 19, 23, 256, 96, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=126)
+_H_GATHER = ConvShape("h_gather", 2, 13, 17, 96, 40, 3, 3, SY=2, SX=1, PT=1, PL=1, PB=1, PR=1, seed=122)
+_H_GEMM = ConvShape("h_gemm", 2, 21, 13, 256, 64, 1, 1, seed=124)
+
+
+@pytest.mark.parametrize("s,plan,family", [
+    (ConvShape("h_regs", 3, 19, 23, 64, 96, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=121), 0, "freg"),
+    (_H_PATCH, hooks.NO_SPLIT, "patch"), (_H_PATCH, 0, "split"), (_H_PATCH, hooks.tile(10), "window_split"),
+    (_H_GATHER, hooks.NO_SPLIT, "gather"), (_H_GATHER, 0, "split"),
+    (ConvShape("h_any", 2, 13, 17, 37, 40, 3, 3, SY=2, SX=1, PT=1, PL=1, PB=1, PR=1, seed=127), hooks.NO_SPLIT, "any"),
+    (ConvShape("h_lowc", 2, 30, 26, 4, 70, 7, 7, SY=2, SX=2, PT=3, PL=3, PB=3, PR=3, seed=123), 0, "lowc"),
+    (_H_GEMM, hooks.NO_SPLIT, "gemm"), (_H_GEMM, 0, "split"), (_H_GATHER, icv.PLAN_VECTOR_ALU, "vector_alu"),
+    (ConvShape("h_i8", 2, 15, 15, 256, 80, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="u8i8", zero_point=64, seed=125), 0, "freg"),
+], ids=lambda v: v.name if hasattr(v, "name") else str(v))
+def test_graph_replays_match_eager(s, plan, family):
     """The conv call is kernel launches only (no allocation, no memset, no synchronisation), so it can be captured;
     every replay, with eager work and synchronisations in between, must give the eager result bit for bit."""
     x, w = make_tensors(s)
-    buf, xd = run_indirect(s, x, w)                 # eager result (also does the one-time function set-up)
+    buf, xd = run_indirect(s, x, w, plan=plan)      # eager result (also does the one-time function set-up)
     check_against_oracle(s, buf.output.cpu().numpy(), x, w)
     eager = buf.output.clone()
     _say("graph", s.name, icv.plan_name(buf.p))
-    assert ("freg" in icv.plan_name(buf.p)) == (s.name in ("h_regs", "h_i8")) and ("split" in icv.plan_name(buf.p)) == (s.name in ("h_patch", "h_gather", "h_gemm"))
+    assert hooks.family(icv.plan_name(buf.p)) == family
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(side):
@@ -801,7 +820,7 @@ def _bf16_bits_to_f64(a: np.ndarray) -> np.ndarray:
 
 
 FUSED_SHAPES = [
-    CONFIGS["cfg1_tiny_f32"],                                                                     # vector-ALU kernel
+    CONFIGS["cfg1_tiny_f32"],
     ConvShape("f_patch", 2, 19, 23, 64, 96, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=91),               # filter in registers, then the pixel-range kernel
     ConvShape("f_gather", 2, 13, 17, 96, 40, 3, 3, SY=2, SX=1, PT=1, PL=1, PB=1, PR=1, seed=92),  # per-element gather
     ConvShape("f_gemm", 3, 7, 11, 128, 72, 1, 1, seed=93),                                        # GEMM on the input
@@ -879,6 +898,12 @@ def test_fused_output_stage_matches_oracle(s, relu, narrow):
     else:
         acc, mag = oracle.conv2d_abs(s, x, w)
     run_fused_case(s, x, w, acc, mag, relu, narrow)
+    # the kernel a split-reduction kernel took the problem from, the vector-ALU kernel
+    for plan in (hooks.NO_SPLIT, icv.PLAN_VECTOR_ALU):
+        name = icv.plan_name(icv.make_params(s, plan=plan))
+        assert (hooks.family(name) == "vector_alu") == (plan == icv.PLAN_VECTOR_ALU) and "split" not in name
+        if name != icv.plan_name(icv.make_params(s)):
+            run_fused_case(s, x, w, acc, mag, relu, narrow, plan=plan)
     # where the library's choice is the filter-in-registers kernel, the pixel-range kernel's fused stage as well
     window = icv.plan_name(icv.make_params(s, plan=icv.PLAN_WINDOW))
     if window and window != icv.plan_name(icv.make_params(s)):
@@ -986,9 +1011,10 @@ def test_im2col_gemm_ablation_with_the_batch_independent_plan(s):
 def test_small_generic_im2col_path():
     s = ConvShape("g_im2col", 2, 9, 10, 5, 7, 3, 3, SY=2, SX=1, PT=1, PL=2, PB=0, PR=1, dtype="f32", dist="uniform", seed=71)
     x, w = make_tensors(s)
-    buf, xd = run_indirect(s, x, w)
-    out2, _ = run_im2col(s, buf, xd)
-    check_against_oracle(s, out2.cpu().numpy(), x, w)
+    for plan in (0, hooks.NO_SPLIT, icv.PLAN_VECTOR_ALU):       # the split-reduction, any-channel-count and vector-ALU kernels
+        buf, xd = run_indirect(s, x, w, plan=plan)
+        out2, _ = run_im2col(s, buf, xd)
+        check_against_oracle(s, out2.cpu().numpy(), x, w)
 
 
 def test_determinism_and_buffer_reuse_with_new_input_pointer():

@@ -56,12 +56,15 @@ def test_small_problems_are_split_and_large_ones_are_not(dtype, C):
     """The library's own choice: same results as the plan it replaces, and no change at a batch that fills the chip."""
     s = ConvShape(f"sp_auto_{dtype}_{C}", 1, 7, 7, C, 96, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype=dtype, seed=740)
     print("conv", s.name, icv.plan_name(icv.make_params(s)), flush=True)
+    assert hooks.family(icv.plan_name(icv.make_params(s))) == "split"
+    assert "split" not in icv.plan_name(icv.make_params(s, plan=NEVER))
     x, w = make_tensors(s)
     buf, _ = run_indirect(s, x, w)
     check_against_oracle(s, buf.output.cpu().numpy(), x, w)
     buf, _ = run_indirect(s, x, w, plan=NEVER)
     check_against_oracle(s, buf.output.cpu().numpy(), x, w)
     big = s.with_(N=512)
+    assert "split" not in icv.plan_name(icv.make_params(big))
     assert icv.plan_name(icv.make_params(big)) == icv.plan_name(icv.make_params(big, plan=NEVER))
     assert icv.packed_filter_bytes(icv.make_params(big)) == icv.packed_filter_bytes(icv.make_params(big, plan=NEVER))
 

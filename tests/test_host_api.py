@@ -193,7 +193,6 @@ def test_plans(lib):
 def test_plan_names_tell_the_kernels_apart(lib):
     """A plan name stands for the kernel that is launched: where a split-reduction kernel takes a problem over, whatever
     plan's buffers it reads, the name is its own; only the vector-ALU kernel is called generic."""
-    import plan_hooks as hooks
     freg32 = ConvShape("n_freg32", 2, 45, 75, 64, 64, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="f32")
     tail = ConvShape("n_any", 1, 8, 8, 37, 8, 3, 3, PT=1, PL=1, PB=1, PR=1)
     point = ConvShape("n_gemm", 2, 21, 13, 256, 64, 1, 1)
@@ -213,9 +212,19 @@ def test_plan_names_tell_the_kernels_apart(lib):
         assert hooks.family(icv.plan_name(icv.make_params(s))) == "lowc"
 
 
+def test_how_many_random_shapes_each_kernel_gets(lib):
+    """The shapes that test_gpu_parity.py runs against the oracle, with the library's choice and without the split-reduction
+    kernels: a change of the dispatch that takes a kernel's coverage away shows here."""
+    from collections import Counter
+    from test_gpu_parity import _random_tensor_core_shapes
+    shapes = _random_tensor_core_shapes()
+    got = {plan: Counter(hooks.family(icv.plan_name(icv.make_params(s, plan=plan))) for s in shapes) for plan in (0, hooks.NO_SPLIT)}
+    assert got[0] == Counter(split=31, any=3, freg=2)
+    assert got[hooks.NO_SPLIT] == Counter(patch=17, gather=17, freg=2)
+
+
 def test_short_fp32_reductions_stay_with_the_filter_in_registers(lib):
     """Problems whose split reduction measured slower keep their own kernel; those that gain most are split."""
-    import plan_hooks as hooks
 
     def fam(n, h, w, C, K, k=3, stride=1, dil=1, plan=0):
         pad = dil * (k // 2)
