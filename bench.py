@@ -36,6 +36,7 @@ LLC_BYTES = 256 << 20
 FETCH_SCALE, WRITE_SCALE = 1.99975, 1.0
 RECORDED_TRAFFIC = {
     # workload: (kernel, FETCH_SIZE KiB, WRITE_SIZE KiB)
+    "cfg1_tiny_f32": ("mfma_f32_split_16x16", 44.5, 2.0),
     "cfg2_3x3_c64": ("mfma_bf16_freg_w2m2", 7713.8, 25090.6),
     "cfg3a_3x3_s2": ("mfma_bf16_freg_w4m1", 15740.5, 25088.0),
     "cfg3b_3x3_d2": ("mfma_bf16_freg_w4m2", 10163.9, 32771.9),

@@ -16,8 +16,8 @@
  *    Calls enqueue work on it and return without synchronising.
  *  - Return value: ICV_OK or a negative icv_status; nothing aborts or throws.
  *    Invalid arguments are detected on the host before anything is launched.
- *  - Base pointers must be 16-byte aligned and pixel strides must make every
- *    pixel row start 16-byte aligned (bf16 / u8i8 tensor-core paths).
+ *  - Base pointers must be 16-byte aligned.  Pixel strides are free; the fastest
+ *    kernels want rows of whole 32- or 64-byte units at 16-byte multiples.
  */
 #ifndef ICV_H
 #define ICV_H
@@ -74,8 +74,10 @@ typedef struct icv_conv_params {
  * ICV_ERR_UNSUPPORTED when the family does not cover the problem. */
 #define ICV_PLAN_VECTOR_ALU 1   /* fp32 vector-ALU kernel, no tensor cores: every dtype, every shape */
 #define ICV_PLAN_GATHER 2       /* tensor cores; each kernel element's rows fetched through their entries, one
-                                   element at a time: the Indirect GEMM of section 2.2 as printed, and the only
-                                   family whose packed filter the im2col + GEMM comparison path reads */
+                                   element at a time: the Indirect GEMM of section 2.2 as printed.  The im2col + GEMM
+                                   comparison path is always available with it, and for aligned rows with the
+                                   kernel tuned for a dense matrix; with other plans it runs where their packed
+                                   filter can be read by a GEMM, at whatever rate that has */
 #define ICV_PLAN_WINDOW 3       /* tensor cores; the input pixels a row tile names are copied to LDS once and
                                    every kernel element reads them there */
 #define ICV_PLAN_FILTER_REGS 4  /* tensor cores; the filter stays in registers and the input slides through LDS
@@ -85,8 +87,10 @@ typedef struct icv_conv_params {
  * n * Hin*Win*pixel stride for image n.  Section 2.3 lists a change of batch size among the events that force the
  * buffer to be (partly) rebuilt; with this bit none is needed: a buffer built with any N serves every N, and N
  * plays no part in the choice of their layout (the packed filter and zero row do not depend on N either; which of the
- * kernels that read that layout runs may depend on it).  The price
- * is a partial last tile per image instead of one per batch. */
+ * kernels that read that layout runs may depend on it).  The price is a partial last tile per image instead of one per
+ * batch, and that layers of few output pixels keep the pixel-range kernel where it is their plan's (4 or more kernel
+ * elements, pixel strides of a power of two bytes, no filter-in-registers kernel): the split-reduction kernels, which the
+ * library prefers there without this bit, read other layouts. */
 #define ICV_PLAN_PER_IMAGE 8
 
 

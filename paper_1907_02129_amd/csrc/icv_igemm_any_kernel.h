@@ -11,17 +11,17 @@
 //    and writes it to one of two LDS buffers.  The rows of stage s + 1 and the entries of stage s + 2 are in flight
 //    while stage s is multiplied; one barrier per stage.
 //  * B comes from global memory in operand order (the packed layout of the filter-in-registers kernel), one coalesced
-//    1 KB read per fragment and wavefront, one stage ahead.  It never touches LDS, whose bandwidth the A fragments
-//    need: with 128 x 128 tiles every B fragment is used for four MFMAs (32 bytes per clock of the 64 that L1 gives)
-//    and every A fragment for one (128 bytes per clock, all that LDS gives).
+//    1 KB read per fragment and wavefront, one stage ahead.  It never touches LDS: a B fragment serves four MFMAs with
+//    128 x 128 tiles (32 bytes per clock of the 64 that L1 gives), two with 128 x 64, one with 64 x 64.
 //
-// Measured (graph replays, one launch): 48 bfloat16 channels, 128 images of 27 x 27, 192 output channels, 3x3: 32.5 us,
-// 476 TFLOP/s (128 x 64 tiles; 33.3 with 128 x 128), where the vector ALUs took 2344 us; 416 uint8 channels, 2 x 78 x 78, 120 output channels: 19.3 us, 565
-// TOP/s; 3 fp32 channels, 16 images of 224 x 224, 7x7 stride 2, whose 12-byte rows are padded to a piece: 120 us from
-// 1115 us.
+// Measured (one launch): 48 bfloat16 channels, 128 images of 27 x 27, 192 output channels, 3x3: 30.6 us, 506 TFLOP/s (128 x 64
+// tiles; 33.3 with 128 x 128), where the vector ALUs took 2344 us; 416 uint8 channels, 2 x 78 x 78, 120 output channels:
+// 19.3 us, 565 TOP/s.  What bounds the first is L1: per stage a workgroup brings 16 KB of rows and 16 KB of filter through
+// it, the counters show 0.91 accesses a busy cycle (MFMA 24 % busy, LDS 24 %, no conflicts).
 //
 // Small workgroups (36 KB of LDS, four wavefronts, no persistence): two to four share a compute unit and hide each
-// other's barriers, first loads and stores.
+// other's barriers, first loads and stores.  A block of entries may have more rows than the tile (the one-image buffer, laid
+// out for the tile of a large batch, serves small ones with smaller tiles).
 //
 // uint8 activations: every A fragment is XORed with 0x80 (x -> x - 128 as a signed byte); the zero row holds the zero
 // point; the filter is zero wherever a piece is padding.
