@@ -440,6 +440,7 @@ int launch_igemm_lowc(const icv_conv_params* p, const Geometry& g, const void* i
         groups = (int)(fill < kb_total ? (fill > groups ? fill : groups) : kb_total);
     }
     a.col_blocks = (kb_total + groups - 1) / groups;
+    groups = (kb_total + a.col_blocks - 1) / a.col_blocks;      // none without columns
     if (groups > 65535) return ICV_ERR_UNSUPPORTED;
     // Teams per workgroup: the path that gathers a whole tile from compact entries in one batch runs several teams
     // on one filter slice (four for the 8-byte rows, two for the wider ones, whose batches need twice the

@@ -137,7 +137,8 @@ def _accumulators(s, x, w):
 
 
 @pytest.mark.parametrize("relu,narrow", [(True, True), (False, True), (True, False)], ids=["relu_narrow", "narrow", "relu"])
-@pytest.mark.parametrize("K,hw", [(40, (23, 19)), (300, (23, 19)), (300, (3, 2)), (70, (130, 131))], ids=["k40", "k300", "k300_one_tile", "many_tiles"])
+@pytest.mark.parametrize("K,hw", [(40, (23, 19)), (300, (23, 19)), (300, (31, 31)), (300, (3, 2)), (70, (130, 131))],
+                         ids=["k40", "k300", "k300_two_blocks", "k300_one_tile", "many_tiles"])
 @pytest.mark.parametrize("dtype,C", [("bf16", 1), ("bf16", 2), ("bf16", 3), ("u8i8", 1), ("u8i8", 2), ("u8i8", 3), ("u8i8", 4),
                                      ("f32", 1), ("f32", 2), ("f32", 3)])
 def test_first_layers_of_few_channels_with_fused_output(dtype, C, K, hw, relu, narrow):
