@@ -370,8 +370,8 @@ __global__ __launch_bounds__(256) void k_igemm_freg(FregArgs g)
             uint32_t m_end = rb_hi * 32u;
             if (m_end > M) m_end = M;
             const int64_t m_base = (int64_t)blk * 32 + 4 * lhalf;
-            const bool whole = (blk + MBE) * 32u <= m_end && k_whole;
-            store_tile<FUSED, I8, MBE, 1>(g.out, acc, (int64_t)m_end, g.K, g.out_stride, m_base, col, whole, ep);
+            const bool whole_rows = (blk + MBE) * 32u <= m_end;
+            store_tile<FUSED, I8, MBE, 1>(g.out, acc, (int64_t)m_end, g.K, g.out_stride, m_base, col, whole_rows && k_whole, whole_rows, ep);
         } else if (blk < rb_hi) {
             // batch-independent buffer: consecutive blocks need not hold consecutive output pixels
 #pragma unroll
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(256) void k_igemm_freg(FregArgs g)
                     acc_t one[1][1];
                     one[0][0] = acc[i][0];
                     store_tile<FUSED, I8, 1, 1>(g.out, one, (int64_t)m1, g.K, g.out_stride, (int64_t)m0 + 4 * lhalf, col,
-                                                m1 - m0 == 32u && k_whole, ep);
+                                                m1 - m0 == 32u && k_whole, m1 - m0 == 32u, ep);
                 }
         }
         asm volatile("" ::: "memory");

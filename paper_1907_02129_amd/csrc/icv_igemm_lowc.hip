@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256 * TEAMS) void k_igemm_lowc(LowcArgs g)
             const int32_t col = col0 + cb * 32 + lrow;
             // register r of lane l holds row 8*(r/4) + 4*(l>>5) + (r&3), column l&31
             const bool whole = whole_rows && col0 + (cb + 1) * 32 <= g.K;
-            store_tile<FUSED, I8, 1, 1>(g.out, block, img_row0 + g.img_rows, g.K, g.out_stride, m_base, col, whole, ep);
+            store_tile<FUSED, I8, 1, 1>(g.out, block, img_row0 + g.img_rows, g.K, g.out_stride, m_base, col, whole, false, ep);
         }
     };
 

@@ -97,14 +97,20 @@ __device__ inline void wait_all_but_stages(int stages)
 // Epilogue of the tensor-core kernels: a wavefront's MB x NB accumulator blocks -> output[row][col].  Register r
 // of lane l of a block holds row 8*(r/4) + 4*(l>>5) + (r&3), column l&31; m_base / n_base are this lane's row
 // and column of register 0 of block (0, 0).
-//   FUSED = false: raw accumulators.  Whole tiles take unguarded non-temporal stores (the output is written once
-//                  and not read again by this kernel), tail tiles guarded ones.
+//   whole          no row or column of the tile lies outside: unguarded non-temporal stores (the output is written once
+//                  and not read again by this kernel).
+//   whole_rows     columns do: they are masked off once per block and its rows stored unguarded, through the caches (the
+//                  neighbouring block's part of a memory line should meet this one there).  Guarded element by element the
+//                  last column tile took longer than all others: 22 x 57 x 57, 32 to 192 channels, 1x1 fp32 59.8 -> 31.3 us,
+//                  37 x 45 x 31, 512 to 112 uint8 27.5 -> 18.2.  (The short-row kernel, whose fused instantiations are short of scalar
+//                  registers, passes false: a third path made 12 x 32 x 32, 16 to 128 channels 7.1 -> 8.6 us.)
+//   FUSED = false: raw accumulators.
 //   FUSED = true : the output stage of icv_conv2d_nhwc_fused (bias, ReLU, narrow output types).  A separate
 //                  instantiation: its per-element work would otherwise raise the plain kernel's register use
 //                  enough to lose the second co-resident workgroup.
 template <bool FUSED, int KIND, int MB, int NB, typename ACC, typename OUT_ACC>
 __device__ inline void store_tile_as(void* outp, const ACC (&acc)[MB][NB], int64_t M, int32_t K, int64_t out_stride,
-                                     int64_t m_base, int32_t n_base, bool whole, const EpilogueArgs& ep)
+                                     int64_t m_base, int32_t n_base, bool whole, bool whole_rows, const EpilogueArgs& ep)
 {
     using store_t = typename std::conditional<KIND == ICV_OUT_BF16, __bf16,
                     typename std::conditional<KIND == ICV_OUT_U8, uint8_t, OUT_ACC>::type>::type;
@@ -131,7 +137,11 @@ __device__ inline void store_tile_as(void* outp, const ACC (&acc)[MB][NB], int64
         for (int j = 0; j < NB; j++) {
             const int32_t col = n_base + j * 32;
             OUT_ACC bias = 0;
-            if constexpr (FUSED) bias = output_bias<OUT_ACC>(ep, col, K);
+            if constexpr (FUSED) {
+                bias = output_bias<OUT_ACC>(ep, col, K);
+                // (its load is waited for here: behind the branches below the wait would be for everything, the store before included)
+                asm volatile("" : "+v"(bias));
+            }
             if (whole) {
                 store_t* o = out + (m_base + i * 32) * out_stride + col;
 #pragma unroll
@@ -140,13 +150,21 @@ __device__ inline void store_tile_as(void* outp, const ACC (&acc)[MB][NB], int64
                     if constexpr (FUSED) { v += bias; if (relu) v = v > (OUT_ACC)0 ? v : (OUT_ACC)0; }
                     __builtin_nontemporal_store(convert(v), &o[(int64_t)(8 * (r >> 2) + (r & 3)) * out_stride]);
                 }
-            } else {
+            } else if (col < K && whole_rows) {
+                store_t* o = out + (m_base + i * 32) * out_stride + col;
+#pragma unroll
+                for (int r = 0; r < 16; r++) {
+                    OUT_ACC v = (OUT_ACC)acc[i][j][r];
+                    if constexpr (FUSED) { v += bias; if (relu) v = v > (OUT_ACC)0 ? v : (OUT_ACC)0; }
+                    o[(int64_t)(8 * (r >> 2) + (r & 3)) * out_stride] = convert(v);
+                }
+            } else if (col < K) {
 #pragma unroll
                 for (int r = 0; r < 16; r++) {
                     const int64_t row = m_base + i * 32 + 8 * (r >> 2) + (r & 3);
                     OUT_ACC v = (OUT_ACC)acc[i][j][r];
                     if constexpr (FUSED) { v += bias; if (relu) v = v > (OUT_ACC)0 ? v : (OUT_ACC)0; }
-                    if (row < M && col < K) out[row * out_stride + col] = convert(v);
+                    if (row < M) out[row * out_stride + col] = convert(v);
                 }
             }
         }
@@ -154,17 +172,17 @@ __device__ inline void store_tile_as(void* outp, const ACC (&acc)[MB][NB], int64
 
 template <bool FUSED, bool I8, int MB, int NB, typename ACC>
 __device__ inline void store_tile(void* out, const ACC (&acc)[MB][NB], int64_t M, int32_t K, int64_t out_stride,
-                                  int64_t m_base, int32_t n_base, bool whole, const EpilogueArgs& ep)
+                                  int64_t m_base, int32_t n_base, bool whole, bool whole_rows, const EpilogueArgs& ep)
 {
     using out_acc_t = typename std::conditional<I8, int32_t, float>::type;
     if constexpr (!FUSED) {
-        store_tile_as<false, ICV_OUT_ACC, MB, NB, ACC, out_acc_t>(out, acc, M, K, out_stride, m_base, n_base, whole, ep);
+        store_tile_as<false, ICV_OUT_ACC, MB, NB, ACC, out_acc_t>(out, acc, M, K, out_stride, m_base, n_base, whole, whole_rows, ep);
     } else if constexpr (I8) {
-        if (ep.out_kind == ICV_OUT_U8) store_tile_as<true, ICV_OUT_U8, MB, NB, ACC, out_acc_t>(out, acc, M, K, out_stride, m_base, n_base, whole, ep);
-        else store_tile_as<true, ICV_OUT_ACC, MB, NB, ACC, out_acc_t>(out, acc, M, K, out_stride, m_base, n_base, whole, ep);
+        if (ep.out_kind == ICV_OUT_U8) store_tile_as<true, ICV_OUT_U8, MB, NB, ACC, out_acc_t>(out, acc, M, K, out_stride, m_base, n_base, whole, whole_rows, ep);
+        else store_tile_as<true, ICV_OUT_ACC, MB, NB, ACC, out_acc_t>(out, acc, M, K, out_stride, m_base, n_base, whole, whole_rows, ep);
     } else {
-        if (ep.out_kind == ICV_OUT_BF16) store_tile_as<true, ICV_OUT_BF16, MB, NB, ACC, out_acc_t>(out, acc, M, K, out_stride, m_base, n_base, whole, ep);
-        else store_tile_as<true, ICV_OUT_ACC, MB, NB, ACC, out_acc_t>(out, acc, M, K, out_stride, m_base, n_base, whole, ep);
+        if (ep.out_kind == ICV_OUT_BF16) store_tile_as<true, ICV_OUT_BF16, MB, NB, ACC, out_acc_t>(out, acc, M, K, out_stride, m_base, n_base, whole, whole_rows, ep);
+        else store_tile_as<true, ICV_OUT_ACC, MB, NB, ACC, out_acc_t>(out, acc, M, K, out_stride, m_base, n_base, whole, whole_rows, ep);
     }
 }
 
