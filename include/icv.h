@@ -88,9 +88,8 @@ typedef struct icv_conv_params {
  * buffer to be (partly) rebuilt; with this bit none is needed: a buffer built with any N serves every N, and N
  * plays no part in the choice of their layout (the packed filter and zero row do not depend on N either; which of the
  * kernels that read that layout runs may depend on it).  The price is a partial last tile per image instead of one per
- * batch, and that layers of few output pixels keep the pixel-range kernel where it is their plan's (4 or more kernel
- * elements, pixel strides of a power of two bytes, no filter-in-registers kernel): the split-reduction kernels, which the
- * library prefers there without this bit, read other layouts. */
+ * batch, and that layers whose window is large (wide rows at stride 2 or with dilation) keep the pixel-range kernel and its tile
+ * for every N. */
 #define ICV_PLAN_PER_IMAGE 8
 
 
@@ -271,7 +270,12 @@ ICV_API int icv_measure_mfma_peak(int32_t dtype, int32_t waves_per_simd, int32_t
  *   mfma_<type>_<tile>..._p<n>         rows gathered per kernel element, aligned rows
  *   mfma_<type>_any_<tile>             rows gathered per kernel element, rows of any length and alignment
  *   mfma_<type>_lowc_<tile>            very short rows, the whole reduction gathered at once
- *   mfma_|gemm_<type>_split_<tile>     the reduction of a tile split over the wavefronts of a workgroup
+ *   mfma_<type>_window_<tile>[_r<n>]_any_<tile> | ..._freg
+ *                                      a tile's input window in LDS, the filter from memory (r: the reduction split over n
+ *                                      wavefronts); then the plan whose buffers it reads: that of the any-channel-count
+ *                                      kernel with this tile, that of the filter in registers
+ *   mfma_|gemm_<type>_split_<tile>     the reduction of a tile split over the wavefronts of a workgroup (32x32: rows in
+ *                                      LDS as in the window kernel, where they fit)
  *   mfma_<type>_<tile>_window_split    the same with the tile's pixel range in LDS
  * With ICV_PLAN_PER_IMAGE the kernel may differ with N where it reads the same buffers.
  */

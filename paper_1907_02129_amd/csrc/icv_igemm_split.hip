@@ -24,7 +24,7 @@ static int slices_for(int64_t tiles, int64_t cus, int stages)
 // of the first in bf16 takes 27.0 against 46.2.  With the window in LDS (icv_igemm_window_split.hip): batch 16 of the first
 // 21.0 -> 12.6, batch 32 21.4 -> 13.0 (uint8 15.6 -> 9.7), batch 64 25.0 against 25.2; 41 x 41, 320 to 208, 5x5 48.4 -> 17.8.  The bfloat16 and uint8 filter-in-registers kernel stays ahead everywhere
 // (5.4 against 6.7 on one 28 x 28 image, 128 to 128 channels).
-int choose_split(const icv_conv_params* p, const Geometry& g)
+int choose_split(const icv_conv_params* p, const Geometry& g, double* us)
 {
     const bool f32 = p->dtype == ICV_F32;
     const int64_t cus = 256;                     // (not the device's: a plan must not depend on where it is made)
@@ -83,9 +83,10 @@ int choose_split(const icv_conv_params* p, const Geometry& g)
             const int64_t tiles = ((g.M + 63) / 64) * ((p->K + 63) / 64);
             const double rounds = (double)((tiles + cus - 1) / cus);
             const double t = 1.2 + rounds * (4.0 + (f32 ? 0.6 : 0.1) * stages);
-            if (t < best_time) best = kChooseWindow;
+            if (t < best_time) { best_time = t; best = kChooseWindow; }
         }
     }
+    *us = best_time;
     return best;
 }
 

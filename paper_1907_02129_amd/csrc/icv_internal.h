@@ -103,6 +103,7 @@ struct Geometry {
     // must not depend on N, but the kernel reads blocks of MR entries with any tile of no more rows, so this one may
     int32_t run_variant;
     int32_t split_tile;      // >= 0: tile of the split-reduction kernel, which then runs instead of the plan's own (same buffers)
+    int32_t win_tile;        // >= 0: tile of the window kernel, which then runs instead of the any-channel-count or split-reduction one
     const char* name;
     EpilogueArgs ep;         // output stage of this call (plain: no bias, no ReLU, accumulator type)
     bool ep_plain;
@@ -181,9 +182,18 @@ constexpr int kChooseWindow = 2;
 size_t window_split_lds_bytes(int T, int64_t row_bytes, int64_t cap_rows);
 int launch_igemm_window_split(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                               const int32_t* ind, void* out, hipStream_t s);
-int choose_split(const icv_conv_params* p, const Geometry& g);
+int choose_split(const icv_conv_params* p, const Geometry& g, double* us);      // us: its time, modelled
 int launch_igemm_split(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                        const int32_t* ind, const void* zero_row, void* out, int a_mode, hipStream_t s);
+// the window kernel: its fastest tile of no more than `block_rows` rows (a tile's entries come from one block of them; block form: 128),
+// with its modelled time, -1 if none fits; whether any does; whether this tile fits (any_size: also where it does not pay)
+constexpr int kNumWindowTiles = 6, kWindowTile32 = 3;
+int choose_window(const icv_conv_params* p, const Geometry& g, int64_t block_rows, double* us);
+bool window_fits(const icv_conv_params* p, const Geometry& g);
+double own_kernel_time(const icv_conv_params* p, const Geometry& g);      // of the kernel the window kernel would stand in for
+bool window_tile_fits(const icv_conv_params* p, const Geometry& g, int tile, bool any_size);
+int launch_igemm_window(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed, const int32_t* ind, void* out,
+                        hipStream_t s);
 int launch_igemm_generic(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                          const int32_t* ind, const void* zero_row, void* out, bool a_direct, hipStream_t s);
 
@@ -194,7 +204,8 @@ struct TileVariant {
 };
 // Test hooks in icv_conv_params::plan above the public bits (icv.h says they must be 0; the library's own tests set
 // them to run every tile and pipeline shape on problems small enough for the CPU oracle): bits 8-11 tile
-// (1 + index into kTileVariants; 9 + tile of the split-reduction kernel, 11 the one with the window in LDS; 15: the plan's own
+// (1 + index into kTileVariants; 9 + tile of the split-reduction kernel, 11 the one with the window in LDS; 12: the
+// window kernel, its tile in bits 12-15 less 2, 0: by the model; 15: the plan's own
 // kernel, that is no split-reduction one and no any-channel-count one for aligned rows), bits 12-15 LDS ring depth of the
 // gathering kernel (2..12), bits 16-17 workgroups per compute unit (1, 2), bits 18-19 stage width (1: 64 bytes, 2: 128 bytes), bits 20-22 kernel elements per
 // pipeline stage of the pixel-range kernel.
