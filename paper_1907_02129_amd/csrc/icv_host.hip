@@ -322,7 +322,8 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     // The window kernel takes a problem from another where its modelled time is 0.85 of the other's -- the models are off by 10 % -- :
     // rows of 16 and 32 bytes from the short-row kernel (always: of 577 drawn problems four were slower, by up to 10 %; on average 1.13
     // times as fast in bfloat16, 1.45 in uint8), from the pixel-range kernel (1.36 in bfloat16, 1.39 in uint8, 2.0 in fp32) and, with rows
-    // of more than three pieces and not in fp32, from the any-channel-count kernel (1.13; 16 of 898 slower by more than 5 %).  A batch-independent layout must not depend on N: the pixel-range kernel's
+    // of more than three pieces and not in fp32, from the any-channel-count kernel (1.13; 16 of 898 slower by more than 5 %), and from the
+    // filter-in-registers kernel in uint8 (1.04).  A batch-independent layout must not depend on N: the pixel-range kernel's
     // problems are compared at eight rounds of tiles there.  The test hook for a plan's own kernel keeps the kernels it replaces on
     // problems that leave compute units idle.
     const bool fills = ((M + 63) / 64) * ((p->K + 63) / 64) >= kCus;
@@ -484,10 +485,11 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         g->name = kWindowNames[p->dtype][g->win_tile][g->kind == PLAN_MFMA_ANY ? g->run_variant : 4];
     } else if (g->split_tile == 1 && !g->gemm_on_input && window_tile_fits(p, *g, kWindowTile32, false)) {
         g->win_tile = kWindowTile32;      // the 32 x 32 tile with its rows in LDS
-    } else if (g->split_tile < 0 && g->kind == PLAN_MFMA_ANY && (window_plan || !(f32 || row_bytes <= 48)) && window_ok()) {
-        g->win_tile = choose_window(p, *g, g->MR, &window_time);
+    } else if (g->split_tile < 0 && (g->kind == PLAN_MFMA_ANY || (g->kind == PLAN_MFMA_FREG && p->dtype == ICV_U8I8)) &&
+               (window_plan || !(g->kind == PLAN_MFMA_ANY && (f32 || row_bytes <= 48))) && window_ok()) {
+        g->win_tile = choose_window(p, *g, g->kind == PLAN_MFMA_ANY ? g->MR : 128, &window_time);
         if (!window_plan && window_time >= 0.85 * own_kernel_time(p, *g)) g->win_tile = -1;
-        if (g->win_tile >= 0) g->name = kWindowNames[p->dtype][g->win_tile][g->run_variant];
+        if (g->win_tile >= 0) g->name = kWindowNames[p->dtype][g->win_tile][g->kind == PLAN_MFMA_ANY ? g->run_variant : 4];
     }
     g->img_rows = g->per_image ? Hout * Wout : M;
     g->img_tiles = (g->img_rows + g->MR - 1) / g->MR;

@@ -157,6 +157,14 @@ double own_kernel_time(const icv_conv_params* p, const Geometry& g)
 {
     const int64_t images = g.per_image ? p->N : 1, img_rows = g.per_image ? (int64_t)g.Hout * g.Wout : g.M;
     const int P = (p->C * g.elem_bytes + 15) / 16;
+    if (g.kind == PLAN_MFMA_FREG) {
+        // uint8 (an XOR per fragment that the window kernel does once per byte; in bfloat16 and fp32 level): row blocks in passes
+        if (p->dtype != ICV_U8I8) return 0.0;
+        const int64_t wn = g.freg_wn, groups = (p->K + 32 * wn - 1) / (32 * wn), ranges = kCus / groups > 1 ? kCus / groups : 1;
+        const int64_t blocks = images * ((img_rows + 31) / 32), per = (blocks + ranges - 1) / ranges;
+        const double passes = (double)((per + 4 / wn - 1) / (4 / wn)), steps = g.T * P / 2.0;
+        return 3.31 + 0.0162 * steps + passes * (0.919 + 0.0271 * steps);
+    }
     int at;
     int64_t mr, nr, span = 0;
     if (g.kind == PLAN_MFMA_ANY) {

@@ -104,7 +104,7 @@ def test_a_row_never_sees_its_neighbours(dtype, C, tile):
 
 
 @pytest.mark.parametrize("dtype,C,K,kernel,plans", [
-    ("bf16", 256, 24, "any", (8,)), ("bf16", 16, 48, "any", (0, 8)), ("u8i8", 32, 256, "any", (0, 8)),
+    ("bf16", 256, 24, "any", (8,)), ("bf16", 16, 48, "any", (0, 8)), ("u8i8", 32, 256, "any", (0, 8)), ("u8i8", 128, 304, "freg", (0, 8)),
     ("bf16", 96, 40, "any", (0, 8)), ("f32", 64, 32, "any", (8,))])
 def test_the_library_chooses_it(dtype, C, K, kernel, plans):
     """Where it is the library's own choice: a large batch, several of its images against the oracle; one image of it."""
