@@ -359,20 +359,21 @@ __global__ __launch_bounds__(256) void k_igemm_freg(FregArgs g)
         // my copies for the next pass (issued during this one) and the stores of the pass before this one
         wait_vmcnt<0>();
         const uint32_t blk = rb_lo + (uint32_t)k * PBK + (uint32_t)(h * MBE);
-        const bool k_whole = (int32_t)(cg * WN + c + 1) * 32 <= g.K;
+        // (a wavefront has one column block: columns past the last are masked here, the output stage then needs two paths, not three)
+        const bool in_k = col < g.K;
         if constexpr (FUSED) {
 #pragma unroll
             for (int i = 0; i < MBE; i++)
 #pragma unroll
                 for (int r = 0; r < 16; r++) acc[i][0][r] += lane_bias;
         }
-        if (blk < rb_hi && !g.img_pixels) {
+        if (blk < rb_hi && !g.img_pixels && in_k) {
             uint32_t m_end = rb_hi * 32u;
             if (m_end > M) m_end = M;
             const int64_t m_base = (int64_t)blk * 32 + 4 * lhalf;
             const bool whole_rows = (blk + MBE) * 32u <= m_end;
-            store_tile<FUSED, I8, MBE, 1>(g.out, acc, (int64_t)m_end, g.K, g.out_stride, m_base, col, whole_rows && k_whole, whole_rows, ep);
-        } else if (blk < rb_hi) {
+            store_tile<FUSED, I8, MBE, 1>(g.out, acc, (int64_t)m_end, g.K, g.out_stride, m_base, col, whole_rows, false, ep);
+        } else if (blk < rb_hi && in_k) {
             // batch-independent buffer: consecutive blocks need not hold consecutive output pixels
 #pragma unroll
             for (int i = 0; i < MBE; i++)
@@ -381,7 +382,7 @@ __global__ __launch_bounds__(256) void k_igemm_freg(FregArgs g)
                     acc_t one[1][1];
                     one[0][0] = acc[i][0];
                     store_tile<FUSED, I8, 1, 1>(g.out, one, (int64_t)m1, g.K, g.out_stride, (int64_t)m0 + 4 * lhalf, col,
-                                                m1 - m0 == 32u && k_whole, m1 - m0 == 32u, ep);
+                                                m1 - m0 == 32u, false, ep);
                 }
         }
         asm volatile("" ::: "memory");
