@@ -321,7 +321,8 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     };
     // The window kernel takes a problem from another where its modelled time is 0.85 of the other's -- the models are off by 10 % -- :
     // rows of 16 and 32 bytes from the short-row kernel (always: of 577 drawn problems four were slower, by up to 10 %; on average 1.13
-    // times as fast in bfloat16, 1.45 in uint8), from the pixel-range kernel (1.36 in bfloat16, 1.39 in uint8, 2.0 in fp32) and, with rows
+    // times as fast in bfloat16, 1.45 in uint8; fewer than four kernel elements in uint8 alone, 1.38 on 97 1x1 problems against 1.06
+    // with 8 of 35 slower in bfloat16), from the pixel-range kernel (1.36 in bfloat16, 1.39 in uint8, 2.0 in fp32) and, with rows
     // of more than three pieces and not in fp32, from the any-channel-count kernel (1.13; 16 of 898 slower by more than 5 %), and from the
     // filter-in-registers kernel in uint8 (1.04).  A batch-independent layout must not depend on N: the pixel-range kernel's
     // problems are compared at eight rounds of tiles there.  The test hook for a plan's own kernel keeps the kernels it replaces on
@@ -330,7 +331,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     int window_known = -1;      // (looked for only where it is asked: a call's host time)
     auto window_ok = [&]() {
         if (window_known < 0)
-            window_known = plan_kernel == 0 && plan_staging == 0 && row_bytes >= 16 && T >= 4 &&
+            window_known = plan_kernel == 0 && plan_staging == 0 && row_bytes >= 16 && (T >= 4 || (lowc_ok && p->dtype == ICV_U8I8)) &&
                            (window_hook || ((hook_tile == 0 || (hook_tile == 15 && fills && !plan_per_image)) && window_fits(p, *g)));
         return window_known == 1;
     };

@@ -31,6 +31,7 @@ def _shapes():
             ("bf16", 1, 1, 5, 32, 9, 2, 2, 1, 1, 1), ("bf16", 2, 23, 20, 128, 100, 3, 3, 1, 1, 1), ("bf16", 1, 40, 61, 96, 66, 3, 3, 1, 1, 0),
             ("u8i8", 3, 13, 11, 64, 70, 3, 3, 1, 1, 1), ("u8i8", 2, 13, 11, 48, 129, 3, 3, 2, 1, 1), ("u8i8", 2, 9, 14, 33, 64, 5, 5, 1, 1, 2),
             ("u8i8", 2, 12, 9, 16, 33, 3, 3, 1, 1, 1), ("u8i8", 1, 11, 12, 417, 40, 3, 3, 1, 1, 1), ("u8i8", 2, 10, 13, 256, 96, 3, 3, 1, 2, 2),
+            ("u8i8", 3, 13, 9, 32, 48, 1, 1, 1, 1, 0), ("u8i8", 2, 11, 13, 16, 70, 1, 1, 2, 1, 1), ("u8i8", 2, 7, 9, 32, 33, 1, 2, 1, 1, 0),
             ("f32", 2, 13, 11, 16, 66, 3, 3, 1, 1, 1), ("f32", 2, 10, 12, 33, 40, 3, 3, 2, 1, 1), ("f32", 1, 9, 10, 4, 20, 4, 4, 1, 1, 2),
             ("f32", 1, 12, 13, 24, 31, 5, 5, 1, 1, 2)]):
         zp = (0, 128, 77)[i % 3] if dtype == "u8i8" else 0
