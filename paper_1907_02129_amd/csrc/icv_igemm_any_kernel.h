@@ -17,7 +17,9 @@
 // Measured (one launch): 48 bfloat16 channels, 128 images of 27 x 27, 192 output channels, 3x3: 30.6 us, 506 TFLOP/s (128 x 64
 // tiles; 33.3 with 128 x 128), where the vector ALUs took 2344 us; 416 uint8 channels, 2 x 78 x 78, 120 output channels:
 // 19.3 us, 565 TOP/s.  What bounds the first is L1: per stage a workgroup brings 16 KB of rows and 16 KB of filter through
-// it, the counters show 0.91 accesses a busy cycle (MFMA 24 % busy, LDS 24 %, no conflicts).
+// it, the counters show 0.91 accesses a busy cycle (MFMA 24 % busy, LDS 24 %, no conflicts).  Both now run on the window kernel
+// (icv_igemm_window_kernel.h: 25.4 and 15.8 us), which reads these buffers; what stays here are pointwise and other kernels of less
+// than four elements, fp32, rows of one to three pieces, windows too large for LDS, and the patch-matrix product.
 //
 // Small workgroups (36 KB of LDS, four wavefronts, no persistence): two to four share a compute unit and hide each
 // other's barriers, first loads and stores.  A block of entries may have more rows than the tile (the one-image buffer, laid

@@ -14,6 +14,9 @@
 //  * Entries are read 2 D stages ahead, so that a row's address is there when its load is issued and the loads in flight
 //    are never drained for one.
 //
+// The 32 x 32 tile runs as the window kernel's (rows in LDS once instead of once per kernel element: 83 x 8 x 12, 336 to 64
+// channels, 5x5 30.2 -> 15.6 us) where its window fits; here remain pointwise layers and windows above 128 KB.
+//
 // Tiles: 16 x 16 (most workgroups: a wavefront's loads are what a small problem waits for) and 32 x 32 (each loaded byte
 // multiplied twice as often).  64 x 64 was tried and taken out: it was ahead in one problem of ninety, by a fifth.  The rule
 // that chooses, with what it measured, is at choose_split in the host file.

@@ -133,7 +133,7 @@ static double window_time(const icv_conv_params* p, const Geometry& g, int tile,
 static bool tile_fits(const icv_conv_params* p, const Geometry& g, int tile, int64_t* cap_rows)
 {
     const int64_t row_bytes = (int64_t)p->C * g.elem_bytes;
-    if (row_bytes < 16 || g.T * row_bytes >= (1ll << 30)) return false;
+    if (row_bytes < 16 || g.T * row_bytes >= (1ll << 27)) return false;      // (32-bit offsets in a column block of the filter)
     *cap_rows = tile_span_bound(p, g.Hout, g.Wout, kWindowTiles[tile].MR);
     return *cap_rows < 65536 && window_chunk(kWindowTiles[tile], g.T, (int)((row_bytes + 15) / 16), *cap_rows, tiles_of(p, g, kWindowTiles[tile])) > 0;
 }

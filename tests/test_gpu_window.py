@@ -120,3 +120,28 @@ def test_the_library_chooses_it(dtype, C, K, kernel, plans):
         buf, _ = run_indirect(s, x, w, plan=plan)
         for n in (0, 23, 47):
             check_against_oracle(one, buf.output[n:n + 1].cpu().numpy(), x[n:n + 1], w)
+
+
+@pytest.mark.parametrize("tile", [0, 3], ids=[TILES[0], TILES[3]])
+def test_graph_replays_match_eager(tile):
+    """Captured once, replayed on new inputs with eager calls in between (LDS above the default limit: set on the first call)."""
+    s = ConvShape("win_graph", 2, 24, 40, 160, 72, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=1060)
+    x, w = make_tensors(s)
+    buf, xd = run_indirect(s, x, w, plan=window(tile))
+    xd = xd.clone()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        icv.run(buf, xd)
+    for i in range(4):
+        xi, _ = make_tensors(s.with_(seed=1061 + i))
+        xd.copy_(icv.to_device(xi))
+        torch.cuda.synchronize()
+        buf.output.fill_(-7)
+        icv.run(buf, xd)
+        torch.cuda.synchronize()
+        eager = buf.output.clone()
+        buf.output.fill_(-7)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(buf.output, eager)
