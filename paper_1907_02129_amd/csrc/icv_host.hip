@@ -444,7 +444,10 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         const int64_t tiles16 = (plan_per_image ? p->N * ((Hout * Wout + 15) / 16) : (M + 15) / 16) * ((p->K + 15) / 16);
         if (g->split_tile >= 0 && !split_hook && g->kind != PLAN_MFMA_FREG && 3 * tiles16 > kCus && window_ok()) {
             const int tile = choose_window(p, *g, g->kind == PLAN_MFMA_ANY ? g->MR : 64, &window_us);
-            if (tile >= 0 && window_us < 0.85 * split_us) g->split_tile = tile == kWindowTile32 ? 1 : -1;
+            if (tile >= 0 && window_us < 0.85 * split_us) {
+                window_plan = tile != kWindowTile32;      // (then it runs whatever the plan's own kernel would take)
+                g->split_tile = window_plan ? -1 : 1;
+            }
         }
         if (g->split_tile == kChooseWindow) {
             g->split_tile = -1;
@@ -474,7 +477,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         if (g->split_tile >= 0) g->name = kSplitNames[p->dtype][g->gemm_on_input][g->split_tile];
     }
     if (g->split_tile < 0 && !plan_per_image && staged_rows() &&
-        (window_hook || (choose_window(p, *g, 64, &window_time) >= 0 && window_time < 0.85 * own_kernel_time(p, *g)))) {
+        (window_hook || window_plan || (choose_window(p, *g, 64, &window_time) >= 0 && window_time < 0.85 * own_kernel_time(p, *g)))) {
         to_any_channels();
         window_plan = true;
     }
@@ -484,7 +487,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         g->win_tile = plan_ring ? plan_ring - 2 : choose_window(p, *g, 128, &window_time);
         if (!window_tile_fits(p, *g, g->win_tile, true)) return ICV_ERR_UNSUPPORTED;
         g->name = kWindowNames[p->dtype][g->win_tile][g->kind == PLAN_MFMA_ANY ? g->run_variant : 4];
-    } else if (g->split_tile == 1 && !g->gemm_on_input && window_tile_fits(p, *g, kWindowTile32, false)) {
+    } else if (g->split_tile == 1 && T >= 4 && !g->gemm_on_input && window_tile_fits(p, *g, kWindowTile32, false)) {
         g->win_tile = kWindowTile32;      // the 32 x 32 tile with its rows in LDS
     } else if (g->split_tile < 0 && (g->kind == PLAN_MFMA_ANY || (g->kind == PLAN_MFMA_FREG && p->dtype == ICV_U8I8)) &&
                (window_plan || !(g->kind == PLAN_MFMA_ANY && (f32 || row_bytes <= 48))) && window_ok()) {
