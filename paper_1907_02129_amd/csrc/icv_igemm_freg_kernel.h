@@ -105,7 +105,11 @@ __device__ __forceinline__ void static_steps(F&& f)
 
 constexpr int freg_slot_bytes(int T, int PBK) { return 1024 + (PBK * T * 64 + 1023) / 1024 * 1024; }
 
-template <int DT, int T, int KS, int WN, int MB, bool FUSED>
+// IMG: the buffer describes one image of the batch (img_pixels > 0).  An instantiation of its own: with both addressings in one kernel
+// the fused ones spilled 7 to 84 scalars (now none in the 3x3 ones of one row block, else up to 49; a batch's up to 64), to vector lanes
+// that a lone wavefront reads back in every pass.  220 drawn problems, graph replays, columns a multiple of 32, split against unsplit: one image's
+// buffer 0.944 bf16, 0.944 uint8, 0.974 fp32; a batch's 0.977, 0.968, 0.994; 32 x 56 x 56, 128 to 256, stride 2, fused 25.4 -> 24.1 us.
+template <int DT, int T, int KS, int WN, int MB, bool FUSED, bool IMG>
 __global__ __launch_bounds__(256) void k_igemm_freg(FregArgs g)
 {
     constexpr bool I8 = DT == ICV_U8I8;      // DT: the icv_dtype of input and filter
@@ -159,12 +163,12 @@ __global__ __launch_bounds__(256) void k_igemm_freg(FregArgs g)
     // b % buf_blocks of image b / buf_blocks, and the last block of an image is partly empty unless the image is a
     // multiple of 32 pixels (its empty rows have zero-row entries and are never stored).
     auto first_row = [&](uint32_t b) -> uint32_t {
-        if (!g.img_pixels) return b * 32u;
+        if (!IMG) return b * 32u;
         const uint32_t n = fast_div(b, g.by_buf);
         return n * g.img_rows + (b - n * g.buf_blocks) * 32u;
     };
     auto end_row = [&](uint32_t b) -> uint32_t {           // one past the last output pixel of block b
-        if (!g.img_pixels) return (b + 1u) * 32u < M ? (b + 1u) * 32u : M;
+        if (!IMG) return (b + 1u) * 32u < M ? (b + 1u) * 32u : M;
         const uint32_t n = fast_div(b, g.by_buf);
         const uint32_t e = (b - n * g.buf_blocks + 1u) * 32u;
         return n * g.img_rows + (e < g.img_rows ? e : g.img_rows);
@@ -208,7 +212,7 @@ __global__ __launch_bounds__(256) void k_igemm_freg(FregArgs g)
         // whole number of blocks
         auto in_buffer = [&](uint32_t blk) {
             if (blk > g.n_blocks - 1) blk = g.n_blocks - 1;
-            return g.img_pixels ? blk - fast_div(blk, g.by_buf) * g.buf_blocks : blk;
+            return IMG ? blk - fast_div(blk, g.by_buf) * g.buf_blocks : blk;
         };
         if (wave == 0) {
             if (lane < PBK) copy16_global_to_lds(rec_base, in_buffer(blk0 + (uint32_t)lane) * 16u, slot);
@@ -218,7 +222,7 @@ __global__ __launch_bounds__(256) void k_igemm_freg(FregArgs g)
             if (((e + 1) & 3) == wave) {
                 const uint32_t o = (uint32_t)e * 1024u + (uint32_t)lane * 16u;      // byte of the pass's entries
                 uint32_t off;
-                if (g.img_pixels) {
+                if constexpr (IMG) {
                     // the pass's blocks need not follow each other in the buffer (the next image starts over at block 0);
                     // a block's entries are T * 64 bytes, a multiple of the 16 bytes a lane moves
                     const uint32_t b = o / (uint32_t)(T * 64);
@@ -291,7 +295,7 @@ __global__ __launch_bounds__(256) void k_igemm_freg(FregArgs g)
 #pragma unroll
         for (int i = 0; i < MBE; i++) {
             delta[i] = *(const int32_t*)(slot + (h * MBE + i) * 16 + 8) - origin;
-            if (g.img_pixels) {
+            if constexpr (IMG) {
                 // the record counts pixels from its image's first one: add the images before it
                 uint32_t b = rb_lo + (uint32_t)k * PBK + (uint32_t)(h * MBE + i);
                 if (b > g.n_blocks - 1) b = g.n_blocks - 1;
@@ -359,22 +363,26 @@ __global__ __launch_bounds__(256) void k_igemm_freg(FregArgs g)
         // my copies for the next pass (issued during this one) and the stores of the pass before this one
         wait_vmcnt<0>();
         const uint32_t blk = rb_lo + (uint32_t)k * PBK + (uint32_t)(h * MBE);
-        // (a wavefront has one column block: columns past the last are masked here, the output stage then needs two paths, not three)
-        const bool in_k = col < g.K;
         if constexpr (FUSED) {
 #pragma unroll
             for (int i = 0; i < MBE; i++)
 #pragma unroll
                 for (int r = 0; r < 16; r++) acc[i][0][r] += lane_bias;
         }
-        if (blk < rb_hi && !g.img_pixels && in_k) {
-            uint32_t m_end = rb_hi * 32u;
-            if (m_end > M) m_end = M;
-            const int64_t m_base = (int64_t)blk * 32 + 4 * lhalf;
-            const bool whole_rows = (blk + MBE) * 32u <= m_end;
-            store_tile<FUSED, I8, MBE, 1>(g.out, acc, (int64_t)m_end, g.K, g.out_stride, m_base, col, whole_rows, false, ep);
-        } else if (blk < rb_hi && in_k) {
-            // batch-independent buffer: consecutive blocks need not hold consecutive output pixels
+        if constexpr (!IMG) {
+            // (a wavefront has one column block: columns past the last are masked here, the output stage then needs two paths, not
+            // three: 1 to 2 % of the kernel where no column is past the last)
+            if (blk < rb_hi && col < g.K) {
+                uint32_t m_end = rb_hi * 32u;
+                if (m_end > M) m_end = M;
+                const int64_t m_base = (int64_t)blk * 32 + 4 * lhalf;
+                const bool whole_rows = (blk + MBE) * 32u <= m_end;
+                store_tile<FUSED, I8, MBE, 1>(g.out, acc, (int64_t)m_end, g.K, g.out_stride, m_base, col, whole_rows, false, ep);
+            }
+        } else if (blk < rb_hi) {
+            // consecutive blocks need not hold consecutive output pixels.  (The mask, live across the address arithmetic of every
+            // block, cost 1 to 2 % here: all three paths)
+            const bool k_whole = (int32_t)(cg * WN + c + 1) * 32 <= g.K;
 #pragma unroll
             for (int i = 0; i < MBE; i++)
                 if (blk + (uint32_t)i < rb_hi) {
@@ -382,7 +390,7 @@ __global__ __launch_bounds__(256) void k_igemm_freg(FregArgs g)
                     acc_t one[1][1];
                     one[0][0] = acc[i][0];
                     store_tile<FUSED, I8, 1, 1>(g.out, one, (int64_t)m1, g.K, g.out_stride, (int64_t)m0 + 4 * lhalf, col,
-                                                m1 - m0 == 32u, false, ep);
+                                                m1 - m0 == 32u && k_whole, m1 - m0 == 32u, ep);
                 }
         }
         asm volatile("" ::: "memory");
@@ -413,10 +421,10 @@ __global__ __launch_bounds__(256) void k_igemm_freg(FregArgs g)
 }
 
 // ------------------------------------------------------------------ launch of one instantiation
-template <int DT, int T, int KS, int WN, int MB, bool FUSED>
+template <int DT, int T, int KS, int WN, int MB, bool FUSED, bool IMG>
 static int launch_one(const FregArgs& a, int64_t grid, size_t lds_bytes, hipStream_t s)
 {
-    auto kern = k_igemm_freg<DT, T, KS, WN, MB, FUSED>;
+    auto kern = k_igemm_freg<DT, T, KS, WN, MB, FUSED, IMG>;
     if (lds_bytes > 64 * 1024) {
         static bool raised[kMaxDevices] = {};      // one array per instantiation of this function template
         const int st = allow_full_lds((const void*)kern, raised);
@@ -430,8 +438,10 @@ static int launch_one(const FregArgs& a, int64_t grid, size_t lds_bytes, hipStre
 template <int DT, bool FUSED, int T, int KS>
 static int launch_shape(const Geometry& g, const FregArgs& a, int64_t grid, size_t lds, hipStream_t s)
 {
-#define ICV_FREG_CASE(WN_, MB_) \
-    if (g.freg_wn == WN_ && g.freg_mb == MB_) return launch_one<DT, T, KS, WN_, MB_, FUSED>(a, grid, lds, s);
+#define ICV_FREG_CASE(WN_, MB_)                                                                              \
+    if (g.freg_wn == WN_ && g.freg_mb == MB_)                                                                \
+        return a.img_pixels ? launch_one<DT, T, KS, WN_, MB_, FUSED, true>(a, grid, lds, s)                  \
+                            : launch_one<DT, T, KS, WN_, MB_, FUSED, false>(a, grid, lds, s);
     ICV_FREG_CASE(4, 2)
     ICV_FREG_CASE(4, 1)
     ICV_FREG_CASE(2, 2)

@@ -104,7 +104,7 @@ __device__ inline void wait_all_but_stages(int stages)
 //                  last column tile took longer than all others: 22 x 57 x 57, 32 to 192 channels, 1x1 fp32 59.8 -> 31.3 us,
 //                  37 x 45 x 31, 512 to 112 uint8 27.5 -> 18.2.  (The short-row kernel, whose fused instantiations are short of scalar
 //                  registers, passes false: a third path made 12 x 32 x 32, 16 to 128 channels 7.1 -> 8.6 us; the
-//                  filter-in-registers kernel, which masks columns itself and was 1 to 2 % slower with it, does too.)
+//                  filter-in-registers kernel masks columns itself where it walks a whole batch, and passes false there.)
 //   FUSED = false: raw accumulators.
 //   FUSED = true : the output stage of icv_conv2d_nhwc_fused (bias, ReLU, narrow output types).  A separate
 //                  instantiation: its per-element work would otherwise raise the plain kernel's register use
