@@ -270,12 +270,11 @@ ICV_API int icv_measure_mfma_peak(int32_t dtype, int32_t waves_per_simd, int32_t
  *   mfma_<type>_<tile>..._p<n>         rows gathered per kernel element, aligned rows
  *   mfma_<type>_any_<tile>             rows gathered per kernel element, rows of any length and alignment
  *   mfma_<type>_lowc_<tile>            very short rows, the whole reduction gathered at once
- *   mfma_<type>_window_<tile>[_r<n>]_any_<tile> | ..._freg
+ *   mfma_<type>_window_<tile>[_r<n>]_any_<tile> | ..._split | ..._freg
  *                                      a tile's input window in LDS, the filter from memory (r: the reduction split over n
  *                                      wavefronts); then the plan whose buffers it reads: that of the any-channel-count
- *                                      kernel with this tile, that of the filter in registers
- *   mfma_|gemm_<type>_split_<tile>     the reduction of a tile split over the wavefronts of a workgroup (32x32: rows in
- *                                      LDS as in the window kernel, where they fit)
+ *                                      kernel with this tile, that of the split-reduction kernel, that of the filter in registers
+ *   mfma_|gemm_<type>_split_<tile>     the reduction of a tile split over the wavefronts of a workgroup
  *   mfma_<type>_<tile>_window_split    the same with the tile's pixel range in LDS
  * With ICV_PLAN_PER_IMAGE the kernel may differ with N where it reads the same buffers.
  */

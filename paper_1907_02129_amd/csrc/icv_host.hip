@@ -81,13 +81,14 @@ static const char* kSplitNames[3][2][2] = {
     {{"mfma_bf16_split_16x16", "mfma_bf16_split_32x32"}, {"gemm_bf16_split_16x16", "gemm_bf16_split_32x32"}},
     {{"mfma_i8_split_16x16", "mfma_i8_split_32x32"}, {"gemm_i8_split_16x16", "gemm_i8_split_32x32"}},
 };
-// the window kernel, [dtype][its tile][plan whose buffers it reads: any-channel-count with this tile, filter in registers]
+// the window kernel, [dtype][its tile][plan whose buffers it reads: any-channel-count with this tile, split-reduction, filter in registers]
 #define ICV_WINDOW_NAMES(T, W) \
-    {"mfma_" T "_window_" W "_any_128x128", "mfma_" T "_window_" W "_any_128x64", "mfma_" T "_window_" W "_any_64x64", "mfma_" T "_window_" W "_any_128x32", "mfma_" T "_window_" W "_freg"}
+    {"mfma_" T "_window_" W "_any_128x128", "mfma_" T "_window_" W "_any_128x64", "mfma_" T "_window_" W "_any_64x64", "mfma_" T "_window_" W "_any_128x32", \
+     "mfma_" T "_window_" W "_split", "mfma_" T "_window_" W "_freg"}
 #define ICV_WINDOW_TILES(T)                                                                                                       \
     {ICV_WINDOW_NAMES(T, "128x64"), ICV_WINDOW_NAMES(T, "64x64"), ICV_WINDOW_NAMES(T, "128x32"), ICV_WINDOW_NAMES(T, "32x32_r8"), \
      ICV_WINDOW_NAMES(T, "64x128"), ICV_WINDOW_NAMES(T, "64x64_r4")}
-static const char* kWindowNames[3][kNumWindowTiles][5] = {ICV_WINDOW_TILES("f32"), ICV_WINDOW_TILES("bf16"), ICV_WINDOW_TILES("i8")};
+static const char* kWindowNames[3][kNumWindowTiles][6] = {ICV_WINDOW_TILES("f32"), ICV_WINDOW_TILES("bf16"), ICV_WINDOW_TILES("i8")};
 static const char* kWindowSplitNames[3] = {"mfma_f32_64x64_window_split", "mfma_bf16_64x64_window_split", "mfma_i8_64x64_window_split"};
 static const char* kLowcNames[3] = {"mfma_f32_lowc_64x64", "mfma_bf16_lowc_64x64", "mfma_i8_lowc_64x64"};
 // filter in registers: [dtype][column blocks per workgroup 1, 2, 4][row blocks per wavefront and pass 1, 2]
@@ -486,15 +487,14 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     if (window_hook && window_ok() && (g->kind == PLAN_MFMA_ANY || g->kind == PLAN_MFMA_FREG)) {
         g->win_tile = plan_ring ? plan_ring - 2 : choose_window(p, *g, 128, &window_time);
         if (!window_tile_fits(p, *g, g->win_tile, true)) return ICV_ERR_UNSUPPORTED;
-        g->name = kWindowNames[p->dtype][g->win_tile][g->kind == PLAN_MFMA_ANY ? g->run_variant : 4];
-    } else if (g->split_tile == 1 && T >= 4 && !g->gemm_on_input && window_tile_fits(p, *g, kWindowTile32, false)) {
+    } else if (g->split_tile == 1 && !split_hook && T >= 4 && !g->gemm_on_input && window_tile_fits(p, *g, kWindowTile32, false)) {
         g->win_tile = kWindowTile32;      // the 32 x 32 tile with its rows in LDS
     } else if (g->split_tile < 0 && (g->kind == PLAN_MFMA_ANY || (g->kind == PLAN_MFMA_FREG && p->dtype == ICV_U8I8)) &&
                (window_plan || !(g->kind == PLAN_MFMA_ANY && (f32 || row_bytes <= 48))) && window_ok()) {
         g->win_tile = choose_window(p, *g, g->kind == PLAN_MFMA_ANY ? g->MR : 128, &window_time);
         if (!window_plan && window_time >= 0.85 * own_kernel_time(p, *g)) g->win_tile = -1;
-        if (g->win_tile >= 0) g->name = kWindowNames[p->dtype][g->win_tile][g->kind == PLAN_MFMA_ANY ? g->run_variant : 4];
     }
+    if (g->win_tile >= 0) g->name = kWindowNames[p->dtype][g->win_tile][g->kind == PLAN_MFMA_ANY ? g->run_variant : 5];
     g->img_rows = g->per_image ? Hout * Wout : M;
     g->img_tiles = (g->img_rows + g->MR - 1) / g->MR;
     g->image_bytes = g->per_image ? (int64_t)p->Hin * p->Win * stride_bytes : 0;

@@ -29,7 +29,7 @@ NO_SPLIT = tile(14)      # neither a split-reduction kernel nor, for aligned row
 
 def family(name: str) -> str:
     """The kernel a plan name stands for (icv.h lists the names)."""
-    for f in ("window_split", "split", "any", "lowc", "freg", "patch"):
+    for f in ("window_split", "window", "split", "any", "lowc", "freg", "patch"):
         if f in name:
             return f
     return {"gene": "vector_alu", "gemm": "gemm", "mfma": "gather"}[name[:4]]

@@ -781,7 +781,7 @@ _H_GEMM = ConvShape("h_gemm", 2, 21, 13, 256, 64, 1, 1, seed=124)
 
 @pytest.mark.parametrize("s,plan,family", [
     (ConvShape("h_regs", 3, 19, 23, 64, 96, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=121), 0, "freg"),
-    (_H_PATCH, hooks.NO_SPLIT, "patch"), (_H_PATCH, 0, "split"), (_H_PATCH, hooks.tile(10), "window_split"),
+    (_H_PATCH, hooks.NO_SPLIT, "patch"), (_H_PATCH, 0, "window"), (_H_PATCH, hooks.tile(10), "window_split"),
     (_H_GATHER, hooks.NO_SPLIT, "gather"), (_H_GATHER, 0, "split"),
     (ConvShape("h_any", 2, 13, 17, 37, 40, 3, 3, SY=2, SX=1, PT=1, PL=1, PB=1, PR=1, seed=127), hooks.NO_SPLIT, "any"),
     (ConvShape("h_lowc", 2, 30, 26, 4, 70, 7, 7, SY=2, SX=2, PT=3, PL=3, PB=3, PR=3, seed=123), 0, "lowc"),

@@ -119,3 +119,21 @@ def test_window_split_matches_oracle(s):
     acc, mag = oracle.conv2d_abs(s, x, w) if s.dtype != "u8i8" else (oracle.conv2d_u8i8(s, x, w, s.zero_point), None)
     for stride in (0, s.K + 3):
         run_fused_case(s, x, w, acc, mag, True, True, plan=WINDOW, out_pixel_stride=stride)
+
+
+@pytest.mark.parametrize("s", [
+    ConvShape("wide_bf16", 3, 53, 54, 416, 11, 3, 3, seed=770),
+    ConvShape("wide_f32", 7, 29, 32, 256, 32, 3, 3, DY=2, DX=2, PT=2, PL=2, PB=2, PR=2, dtype="f32", seed=771),
+    ConvShape("wide_u8", 1, 82, 82, 240, 32, 5, 5, dtype="u8i8", zero_point=77, seed=772),
+], ids=lambda s: s.name)
+def test_the_library_chooses_32x32_tiles_for_wide_rows(s):
+    """Windows above 128 KB: rows gathered through 32-bit entries.  (Where the window is smaller the window kernel's 32 x 32 tile
+    takes the problem, under a name of its own.)"""
+    name = icv.plan_name(icv.make_params(s))
+    print("conv", s.name, name, flush=True)
+    assert name == {"bf16": "mfma_bf16_split_32x32", "f32": "mfma_f32_split_32x32", "u8i8": "mfma_i8_split_32x32"}[s.dtype]
+    row = s.C * {"bf16": 2, "f32": 4, "u8i8": 1}[s.dtype]
+    assert icv.tile_span_bound(icv.make_params(s), 32) * row > 128 * 1024
+    x, w = make_tensors(s)
+    buf, _ = run_indirect(s, x, w)
+    check_against_oracle(s, buf.output.cpu().numpy(), x, w)

@@ -191,14 +191,14 @@ def test_plans(lib):
 
 
 def test_plan_names_tell_the_kernels_apart(lib):
-    """A plan name stands for the kernel that is launched: where a split-reduction kernel takes a problem over, whatever
-    plan's buffers it reads, the name is its own; only the vector-ALU kernel is called generic."""
+    """A plan name stands for the kernel that is launched: where a split-reduction kernel or the window kernel takes a problem
+    over, whatever plan's buffers it reads, the name is its own; only the vector-ALU kernel is called generic."""
     freg32 = ConvShape("n_freg32", 2, 45, 75, 64, 64, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="f32")
     tail = ConvShape("n_any", 1, 8, 8, 37, 8, 3, 3, PT=1, PL=1, PB=1, PR=1)
     point = ConvShape("n_gemm", 2, 21, 13, 256, 64, 1, 1)
     gather = ConvShape("n_gather", 2, 13, 17, 96, 40, 3, 3, PT=1, PL=1, PB=1, PR=1)
     window = ConvShape("n_window", 32, 7, 7, 512, 512, 3, 3, PT=1, PL=1, PB=1, PR=1)
-    for s, split, own in ((freg32, "mfma_f32_split_32x32", "freg"), (tail, "mfma_bf16_split_16x16", "any"),
+    for s, split, own in ((freg32, "mfma_f32_window_32x32_r8_freg", "freg"), (tail, "mfma_bf16_split_16x16", "any"),
                           (point, "gemm_bf16_split_16x16", "gemm"), (gather, "mfma_bf16_split_16x16", "gather"),
                           (window, "mfma_bf16_64x64_window_split", "patch")):
         assert icv.plan_name(icv.make_params(s)) == split, s.name
@@ -235,7 +235,7 @@ def test_short_fp32_reductions_stay_with_the_filter_in_registers(lib):
               (1, 46, 46, 16, 128, 3, 1, 2), (4, 30, 23, 32, 107), (13, 36, 36, 32, 64, 3, 2), (2, 53, 33, 16, 126, 5)):
         assert fam(*p) == "freg", p
     for p in ((1, 14, 14, 64, 128), (2, 45, 75, 64, 64), (1, 7, 7, 32, 512), (1, 28, 28, 16, 64, 5)):
-        assert fam(*p) == "split", p
+        assert fam(*p) in ("split", "window"), p
 
 
 @pytest.mark.parametrize("C,K", [(320, 480), (90, 192), (96, 64), (37, 300), (112, 31)])
@@ -250,7 +250,7 @@ def test_batch_independent_layout_serves_the_tile_of_every_batch_size(lib, C, K)
         L = icv.get_indirection_layout(p)
         layouts.add((L.tile_rows, L.tiles, icv.indirection_bytes(p), icv.packed_filter_bytes(p), icv.zero_row_bytes(p)))
     assert len(layouts) == 1
-    assert any("split" in n for n in names)
+    assert any(hooks.family(n) == "split" or "_window_32x32_r8_" in n for n in names), names
     assert any(n.endswith("any_128x32" if K <= 32 else ("any_128x128", "any_128x64")) for n in names), names
 
 
