@@ -136,14 +136,14 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     const int algo = p->plan & 7, plan_per_image = (p->plan >> 3) & 1;
     const int hook_tile = (p->plan >> 8) & 15, plan_ring = (p->plan >> 12) & 15, plan_per_cu = (p->plan >> 16) & 3,
               plan_kcb = (p->plan >> 18) & 3, plan_group = (p->plan >> 20) & 7;
-    const bool split_hook = hook_tile > kNumTileVariants, window_hook = hook_tile == 12;
+    const bool split_hook = hook_tile >= 9 && hook_tile <= 11, window_hook = hook_tile == 12, any_hook = hook_tile == 13;
     if (p->plan < 0 || p->plan >= (1 << 23) || (p->plan & 0xF0) != 0 || algo > ICV_PLAN_FILTER_REGS ||
-        (hook_tile > kNumTileVariants && (hook_tile < 9 || hook_tile > 12) && hook_tile != 15) || (hook_tile && algo == ICV_PLAN_VECTOR_ALU) || plan_ring == 1 || plan_ring > 12 ||
+        (hook_tile > kNumTileVariants && (hook_tile < 9 || hook_tile == 14)) || (hook_tile && algo == ICV_PLAN_VECTOR_ALU) || plan_ring == 1 || plan_ring > 12 ||
         plan_per_cu > 2 || plan_kcb > 2)
         return ICV_ERR_INVALID_ARG;
     // 0: the library chooses; 1: rows gathered per kernel element; 2: the tile's pixel range in LDS; 3: filter in registers
     const int plan_staging = algo == ICV_PLAN_GATHER ? 1 : (algo == ICV_PLAN_WINDOW ? 2 : (algo == ICV_PLAN_FILTER_REGS ? 3 : 0));
-    const int plan_kernel = algo == ICV_PLAN_VECTOR_ALU ? 1 : (hook_tile && !split_hook ? hook_tile + 1 : 0);
+    const int plan_kernel = algo == ICV_PLAN_VECTOR_ALU ? 1 : (hook_tile && hook_tile <= kNumTileVariants ? hook_tile + 1 : 0);
 
     const int64_t Hout = out_extent(p->Hin, p->PT, p->PB, p->DY, p->R, p->SY);
     const int64_t Wout = out_extent(p->Win, p->PL, p->PR, p->DX, p->S, p->SX);
@@ -326,18 +326,18 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     // with 8 of 35 slower in bfloat16), from the pixel-range kernel (1.36 in bfloat16, 1.39 in uint8, 2.0 in fp32) and, with rows
     // of more than three pieces and not in fp32, from the any-channel-count kernel (1.13; 16 of 898 slower by more than 5 %), and from the
     // filter-in-registers kernel in uint8 (1.04).  A batch-independent layout must not depend on N: the pixel-range kernel's
-    // problems are compared at eight rounds of tiles there.  The test hook for a plan's own kernel keeps the kernels it replaces on
-    // problems that leave compute units idle.
-    const bool fills = ((M + 63) / 64) * ((p->K + 63) / 64) >= kCus;
+    // problems are compared at eight rounds of tiles there.
     int window_known = -1;      // (looked for only where it is asked: a call's host time)
     auto window_ok = [&]() {
         if (window_known < 0)
             window_known = plan_kernel == 0 && plan_staging == 0 && row_bytes >= 16 && (T >= 4 || (lowc_ok && p->dtype == ICV_U8I8)) &&
-                           (window_hook || ((hook_tile == 0 || (hook_tile == 15 && fills && !plan_per_image)) && window_fits(p, *g)));
+                           (window_hook || (hook_tile == 0 && window_fits(p, *g)));
         return window_known == 1;
     };
     bool window_plan = false;
-    if (freg_mb) {
+    if (any_hook && plan_staging == 0 && T * row_bytes < (1ll << 31)) {
+        to_any_channels();
+    } else if (freg_mb) {
         g->kind = PLAN_MFMA_FREG;
         g->variant = -1;
         g->MR = 32;
@@ -350,7 +350,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         g->n_stages = g->T;
         g->zero_row_number = 0xFFFFu;
         g->name = kFregNames[p->dtype][freg_wn == 4 ? 2 : freg_wn - 1][freg_mb - 1];
-    } else if (lowc_ok && row_bytes >= 16 && !f32 && (hook_tile == 0 || window_hook) && window_ok()) {
+    } else if (lowc_ok && row_bytes >= 16 && !f32 && window_ok()) {
         to_any_channels();
         window_plan = true;
     } else if (lowc_ok) {
@@ -436,7 +436,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     double window_time = 0.0;
     g->split_tile = -1;
     g->per_image = plan_per_image && !g->gemm_on_input ? 1 : 0;      // the GEMM on the input tensor reads no entries
-    if (plan_kernel == 0 && plan_staging == 0 && row_bytes >= 16 && T * row_bytes < (1ll << 31) && hook_tile != 15 && !window_hook &&
+    if (plan_kernel == 0 && plan_staging == 0 && row_bytes >= 16 && T * row_bytes < (1ll << 31) && hook_tile != 15 && !window_hook && !any_hook &&
         (g->kind == PLAN_MFMA_FREG || g->kind == PLAN_MFMA_ANY || (g->kind == PLAN_MFMA && !plan_per_image))) {
         double split_us = 0.0, window_us = 0.0;
         g->split_tile = split_hook ? hook_tile - 9 : choose_split(p, *g, &split_us);
@@ -466,7 +466,8 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
                 g->stages_per_tap = 1; g->taps_per_stage = 1; g->n_stages = g->T;
             }
         }
-        if (g->split_tile >= 0 && g->kind == PLAN_MFMA) {
+        // (the 32 x 32 tile has no instantiation for entries in block form: asked for, it takes a layout of its own there too)
+        if (g->split_tile >= 0 && (g->kind == PLAN_MFMA || (split_hook && g->split_tile == 1 && g->kind == PLAN_MFMA_FREG))) {
             g->kind = PLAN_MFMA_ANY;
             g->variant = g->run_variant = kAnySplitTile;
             g->MR = kAnyTiles[kAnySplitTile].MR;
@@ -488,7 +489,9 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         g->win_tile = plan_ring ? plan_ring - 2 : choose_window(p, *g, 128, &window_time);
         if (!window_tile_fits(p, *g, g->win_tile, true)) return ICV_ERR_UNSUPPORTED;
     } else if (g->split_tile == 1 && !split_hook && T >= 4 && !g->gemm_on_input && window_tile_fits(p, *g, kWindowTile32, false)) {
-        g->win_tile = kWindowTile32;      // the 32 x 32 tile with its rows in LDS
+        // the 32 x 32 tile with its rows in LDS.  (Always where the filter is in registers: its ring, a power of two of pixel rows
+        // in 160 KB, holds the pixels of 64 output pixels or more, so 32 of them never need over 128 KB.)
+        g->win_tile = kWindowTile32;
     } else if (g->split_tile < 0 && (g->kind == PLAN_MFMA_ANY || (g->kind == PLAN_MFMA_FREG && p->dtype == ICV_U8I8)) &&
                (window_plan || !(g->kind == PLAN_MFMA_ANY && (f32 || row_bytes <= 48))) && window_ok()) {
         g->win_tile = choose_window(p, *g, g->kind == PLAN_MFMA_ANY ? g->MR : 128, &window_time);

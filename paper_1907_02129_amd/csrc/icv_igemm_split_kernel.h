@@ -316,10 +316,10 @@ static int launch_split_one(const SplitArgs& a, hipStream_t s)
 template <int DT, int BLK, int D>
 static int launch_split_tile(const SplitArgs& a, int rows, bool tail, hipStream_t s)
 {
-    if (rows == SPLIT_BLOCK16) {
-        if (tail) return ICV_ERR_UNSUPPORTED;
-        return launch_split_one<DT, BLK, D, false, SPLIT_BLOCK16>(a, s);
+    if constexpr (BLK == 16) {      // (32 x 32 tiles of such a plan are the window kernel's)
+        if (rows == SPLIT_BLOCK16) return tail ? ICV_ERR_UNSUPPORTED : launch_split_one<DT, BLK, D, false, SPLIT_BLOCK16>(a, s);
     }
+    if (rows == SPLIT_BLOCK16) return ICV_ERR_UNSUPPORTED;
     if (rows == SPLIT_INT32)
         return tail ? launch_split_one<DT, BLK, D, true, SPLIT_INT32>(a, s)
                     : launch_split_one<DT, BLK, D, false, SPLIT_INT32>(a, s);

@@ -225,7 +225,7 @@ __global__ __launch_bounds__(64 * WM * WN * WS, 2) void k_igemm_window(WindowArg
 #pragma unroll
             for (int i = 0; i < MB; i++) af[0][i] = *(const uint4*)(lds + at[i]);
             // (both unrolled to whole rings and pairs of fragment buffers)
-            constexpr int STAGES = U == 4 ? 1 : (U == 1 ? 4 : 2);
+            constexpr int STAGES = U == 4 ? 1 : 2;
             auto stage = [&](int k) __attribute__((always_inline)) {
                 uint32_t next[MB];
                 if (++r == S) {

@@ -205,8 +205,8 @@ struct TileVariant {
 // Test hooks in icv_conv_params::plan above the public bits (icv.h says they must be 0; the library's own tests set
 // them to run every tile and pipeline shape on problems small enough for the CPU oracle): bits 8-11 tile
 // (1 + index into kTileVariants; 9 + tile of the split-reduction kernel, 11 the one with the window in LDS; 12: the
-// window kernel, its tile in bits 12-15 less 2, 0: by the model; 15: the plan's own
-// kernel, that is no split-reduction one and no any-channel-count one for aligned rows), bits 12-15 LDS ring depth of the
+// window kernel, its tile in bits 12-15 less 2, 0: by the model; 13: the any-channel-count kernel, aligned rows or not; 15: the plan's own
+// kernel, that is no split-reduction one, no window one and no any-channel-count one for aligned rows), bits 12-15 LDS ring depth of the
 // gathering kernel (2..12), bits 16-17 workgroups per compute unit (1, 2), bits 18-19 stage width (1: 64 bytes, 2: 128 bytes), bits 20-22 kernel elements per
 // pipeline stage of the pixel-range kernel.
 extern const TileVariant kTileVariants[];

@@ -24,7 +24,9 @@ def group(taps: int) -> int:
     return taps << 20
 
 
-NO_SPLIT = tile(14)      # neither a split-reduction kernel nor, for aligned rows, the any-channel-count one: the plan's own kernel
+# neither a split-reduction kernel nor the window kernel nor, for aligned rows, the any-channel-count one: the plan's own kernel
+NO_SPLIT = tile(14)
+ANY = tile(12)           # the any-channel-count kernel, whatever the rows, at any number of output pixels
 
 
 def family(name: str) -> str:

@@ -15,6 +15,9 @@ from test_gpu_parity import check_against_oracle, run_fused_case, run_im2col, ru
 pytestmark = pytest.mark.gpu
 
 
+DT = {"bf16": "bf16", "u8i8": "i8", "f32": "f32"}         # a plan name's type
+
+
 def _shapes():
     out = []
     # channels: bytes per row below, at and above whole 16-byte pieces; K: one, two and more column blocks, ragged
@@ -35,12 +38,12 @@ def _shapes():
     return out
 
 
-@pytest.mark.parametrize("plan", [0, icv.PLAN_PER_IMAGE, icv.PLAN_GATHER], ids=["auto", "per_image", "gather"])
+@pytest.mark.parametrize("plan", [0, icv.PLAN_PER_IMAGE, icv.PLAN_GATHER, hooks.ANY], ids=["auto", "per_image", "gather", "any"])
 @pytest.mark.parametrize("s", _shapes(), ids=lambda s: s.name)
 def test_any_channel_count_matches_oracle(s, plan):
     name = icv.plan_name(icv.make_params(s, plan=plan))
     print("conv", s.name, name, flush=True)
-    assert hooks.family(name) in ("any", "split", "lowc")
+    assert hooks.family(name) in (("any",) if plan == hooks.ANY else ("any", "split", "lowc", "window"))
     x, w = make_tensors(s)
     buf, xd = run_indirect(s, x, w, plan=plan)
     check_against_oracle(s, buf.output.cpu().numpy(), x, w)
@@ -79,20 +82,43 @@ def test_a_row_never_sees_its_neighbours(dtype, C):
     (ConvShape("one_f32", 1, 61, 67, 48, 136, 2, 2, dtype="f32", seed=638), {1: "64x64", 14: "128x64"}),
 ], ids=lambda v: v.name if hasattr(v, "name") else "")
 def test_one_image_buffer_under_every_tile(s, tiles):
+    """With the any-channel-count kernel itself, and with the library's choice among the kernels that read the buffer."""
     x1, w = make_tensors(s)
-    built = icv.prepare(s, icv.to_device(w), plan=icv.PLAN_PER_IMAGE)
-    torch.cuda.synchronize()
-    for n, tile in tiles.items():
-        big = s.with_(N=n)
-        x, _ = make_tensors(big)
-        p = icv.make_params(big, plan=icv.PLAN_PER_IMAGE)
-        print("conv", s.name, n, icv.plan_name(p), flush=True)
-        assert icv.plan_name(p).endswith("any_" + tile), icv.plan_name(p)
-        out = torch.full((n, built.Hout, built.Wout, s.K), -7, dtype=built.output.dtype, device="cuda:0")
-        icv.conv2d_nhwc(p, icv.to_device(x), built.packed, built.indirection, built.zero_row, out)
+    for plan in (icv.PLAN_PER_IMAGE | hooks.ANY, icv.PLAN_PER_IMAGE):
+        built = icv.prepare(s, icv.to_device(w), plan=plan)
         torch.cuda.synchronize()
-        for i in sorted({0, n - 1}):
-            check_against_oracle(s, out[i:i + 1].cpu().numpy(), x[i:i + 1], w)
+        for n, tile in tiles.items():
+            big = s.with_(N=n)
+            x, _ = make_tensors(big)
+            p = icv.make_params(big, plan=plan)
+            print("conv", s.name, n, icv.plan_name(p), flush=True)
+            if plan & hooks.ANY:
+                assert icv.plan_name(p) == f"mfma_{DT[s.dtype]}_any_{tile}"
+            else:
+                assert hooks.family(icv.plan_name(p)) == ("window" if s.name == "one_rows" else "any")
+            out = torch.full((n, built.Hout, built.Wout, s.K), -7, dtype=built.output.dtype, device="cuda:0")
+            icv.conv2d_nhwc(p, icv.to_device(x), built.packed, built.indirection, built.zero_row, out)
+            torch.cuda.synchronize()
+            for i in sorted({0, n - 1}):
+                check_against_oracle(s, out[i:i + 1].cpu().numpy(), x[i:i + 1], w)
+
+
+@pytest.mark.parametrize("s,tile,per_image", [
+    (ConvShape("lib_128x128", 34, 31, 31, 24, 256, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=641), "128x128", True),
+    (ConvShape("lib_128x64", 51, 50, 50, 24, 64, 3, 3, seed=642), "128x64", True),
+    (ConvShape("lib_128x128_u8", 40, 84, 84, 40, 96, 3, 3, SY=2, SX=2, PT=1, PL=1, PB=1, PR=1, dtype="u8i8", zero_point=7, seed=643), "128x128", False),
+    (ConvShape("lib_128x64_f32", 39, 56, 56, 4, 64, 5, 5, PT=2, PL=2, PB=2, PR=2, dtype="f32", seed=644), "128x64", False),
+], ids=lambda v: getattr(v, "name", ""))
+def test_large_tiles_where_the_library_chooses_them(s, tile, per_image):
+    """Rows of one to three pieces, whose window the window kernel does not take."""
+    plan = icv.PLAN_PER_IMAGE if per_image else 0
+    assert icv.plan_name(icv.make_params(s, plan=plan)) == f"mfma_{DT[s.dtype]}_any_{tile}"
+    print("conv", s.name, flush=True)
+    x, w = make_tensors(s)
+    buf, _ = run_indirect(s, x, w, plan=plan)
+    one = s.with_(N=1)
+    for n in (0, s.N // 2, s.N - 1):
+        check_against_oracle(one, buf.output[n:n + 1].cpu().numpy(), x[n:n + 1], w)
 
 
 @pytest.mark.parametrize("plan", [0, icv.PLAN_PER_IMAGE, icv.PLAN_GATHER], ids=["auto", "per_image", "gather"])
@@ -153,6 +179,26 @@ def test_first_layers_of_few_channels_with_fused_output(dtype, C, K, hw, relu, n
         run_fused_case(s, x, w, acc, mag, relu, narrow, plan=plan, out_pixel_stride=K + 3)
 
 
+@pytest.mark.parametrize("k", [(1, 1), (3, 3)], ids=["1x1", "3x3"])
+@pytest.mark.parametrize("dtype,C", [("bf16", 8), ("bf16", 16), ("u8i8", 16), ("u8i8", 32)])
+def test_short_rows_of_16_and_32_bytes(dtype, C, k):
+    """Compact entries and rows of whole pieces in the short-row kernel, which keeps them where the window kernel does not take
+    them: bfloat16 pointwise layers by the library's choice, the others by the hook."""
+    s = ConvShape(f"short_{dtype}_c{C}", 3, 23, 19, C, 70, *k, SY=2, PT=k[0] // 2, PL=k[1] // 2, PB=1, PR=2, dtype=dtype,
+                  zero_point=3 * C if dtype == "u8i8" else 0, seed=655)
+    x, w = make_tensors(s)
+    acc, mag = _accumulators(s, x, w)
+    for per_image in (0, icv.PLAN_PER_IMAGE):
+        p = icv.make_params(s, plan=hooks.NO_SPLIT | per_image)
+        print("conv", s.name, icv.plan_name(p), flush=True)
+        assert hooks.family(icv.plan_name(p)) == "lowc" and icv.get_indirection_layout(p).entry_bytes == 2
+        if dtype == "bf16" and k == (1, 1):
+            assert icv.plan_name(icv.make_params(s, plan=per_image)) == icv.plan_name(p)
+        buf, _ = run_indirect(s, x, w, plan=hooks.NO_SPLIT | per_image)
+        check_against_oracle(s, buf.output.cpu().numpy(), x, w)
+        run_fused_case(s, x, w, acc, mag, True, True, plan=hooks.NO_SPLIT | per_image, out_pixel_stride=73)
+
+
 _FUSED = [
     # (shape, tile): every tile with whole rows and with a padded last piece, rows shorter than a piece, dense rows
     (ConvShape("fu_128x128_whole", 3, 150, 147, 24, 70, 1, 2, seed=681), "any_128x128"),
@@ -180,29 +226,34 @@ def test_fused_output_of_every_tile(s, tile, relu, narrow):
     x, w = make_tensors(s)
     acc, mag = _accumulators(s, x, w)
     for plan in (hooks.NO_SPLIT, hooks.NO_SPLIT | icv.PLAN_PER_IMAGE):
-        assert icv.plan_name(icv.make_params(s, plan=plan)).endswith(tile)
+        assert icv.plan_name(icv.make_params(s, plan=plan)) == f"mfma_{DT[s.dtype]}_{tile}"
         run_fused_case(s, x, w, acc, mag, relu, narrow, plan=plan, out_pixel_stride=s.K + 5)
 
 
 @pytest.mark.parametrize("plan", [0, icv.PLAN_PER_IMAGE], ids=["auto", "per_image"])
 @pytest.mark.parametrize("dtype,C,K", [("bf16", 96, 140), ("bf16", 96, 64), ("bf16", 160, 24), ("u8i8", 192, 70), ("f32", 48, 33)])
 def test_aligned_rows_that_are_gathered_per_kernel_element(dtype, C, K, plan):
-    """Rows of whole 64-byte units that no power of two fits take the same kernel (and few output pixels the split-reduction
-    kernel), checked on several images of a large batch too, where the larger tiles run."""
+    """Rows of whole 64-byte units that no power of two fits: the any-channel-count kernel itself, whose larger tiles run on a
+    large batch, and what the library chooses on that kernel's buffers."""
     s = ConvShape(f"rows_{dtype}_{C}", 5, 45, 47, C, K, 3, 3, SY=1 + (K == 24), PT=1, PL=1, PB=1, PR=1, dtype=dtype,
                   zero_point=11 if dtype == "u8i8" else 0, seed=670)
     name = icv.plan_name(icv.make_params(s, plan=plan))
     print("conv", s.name, name, flush=True)
-    assert name.endswith(("window_32x32_r8_split", "window_32x32_r8_any_128x32") if C == 160 else "any_64x64"), name
+    assert hooks.family(name) in ("any", "window")
     big = s.with_(N=40)
     tile = {("bf16", 96): "128x64", ("bf16", 160): "128x32", ("u8i8", 192): "128x128", ("f32", 48): "128x64"}[dtype, C]
-    assert icv.plan_name(icv.make_params(big, plan=plan)).endswith("any_" + tile)
+    assert icv.plan_name(icv.make_params(s, plan=plan | hooks.ANY)) == f"mfma_{DT[dtype]}_any_" + ("128x32" if C == 160 else "64x64")
+    assert icv.plan_name(icv.make_params(big, plan=plan | hooks.ANY)) == f"mfma_{DT[dtype]}_any_{tile}"
+    assert hooks.family(icv.plan_name(icv.make_params(big, plan=plan))) == ("any" if dtype == "f32" else "window")
     xb, wb = make_tensors(big)
-    bbuf, _ = run_indirect(big, xb, wb, plan=plan)
     one = s.with_(N=1)
-    for n in (0, 17, 39):
-        check_against_oracle(one, bbuf.output[n:n + 1].cpu().numpy(), xb[n:n + 1], wb)
+    for hook in (0, hooks.ANY):
+        bbuf, _ = run_indirect(big, xb, wb, plan=plan | hook)
+        for n in (0, 17, 39):
+            check_against_oracle(one, bbuf.output[n:n + 1].cpu().numpy(), xb[n:n + 1], wb)
     x, w = make_tensors(s)
+    buf, _ = run_indirect(s, x, w, plan=plan | hooks.ANY)
+    check_against_oracle(s, buf.output.cpu().numpy(), x, w)
     buf, xd = run_indirect(s, x, w, plan=plan)
     check_against_oracle(s, buf.output.cpu().numpy(), x, w)
     gathered, _ = run_indirect(s, x, w, plan=icv.PLAN_GATHER | plan)

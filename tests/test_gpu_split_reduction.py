@@ -53,7 +53,8 @@ def test_split_reduction_matches_oracle(s, per_image, tile):
 
 @pytest.mark.parametrize("dtype,C", [("bf16", 512), ("u8i8", 416), ("f32", 64), ("f32", 100)])
 def test_small_problems_are_split_and_large_ones_are_not(dtype, C):
-    """The library's own choice: same results as the plan it replaces, and no change at a batch that fills the chip."""
+    """The library's own choice: same results as the plan it replaces, and no split at a batch that fills the chip (which the
+    window kernel may take)."""
     s = ConvShape(f"sp_auto_{dtype}_{C}", 1, 7, 7, C, 96, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype=dtype, seed=740)
     print("conv", s.name, icv.plan_name(icv.make_params(s)), flush=True)
     assert hooks.family(icv.plan_name(icv.make_params(s))) == "split"
@@ -65,8 +66,10 @@ def test_small_problems_are_split_and_large_ones_are_not(dtype, C):
     check_against_oracle(s, buf.output.cpu().numpy(), x, w)
     big = s.with_(N=512)
     assert "split" not in icv.plan_name(icv.make_params(big))
-    assert icv.plan_name(icv.make_params(big)) == icv.plan_name(icv.make_params(big, plan=NEVER))
-    assert icv.packed_filter_bytes(icv.make_params(big)) == icv.packed_filter_bytes(icv.make_params(big, plan=NEVER))
+    assert hooks.family(icv.plan_name(icv.make_params(big, plan=NEVER))) == {512: "patch", 416: "any", 64: "freg", 100: "any"}[C]
+    if hooks.family(icv.plan_name(icv.make_params(big))) != "window":
+        assert icv.plan_name(icv.make_params(big)) == icv.plan_name(icv.make_params(big, plan=NEVER))
+        assert icv.packed_filter_bytes(icv.make_params(big)) == icv.packed_filter_bytes(icv.make_params(big, plan=NEVER))
 
 
 @pytest.mark.parametrize("tile", [TILE16, TILE32], ids=["16x16", "32x32"])

@@ -207,6 +207,10 @@ def test_plan_names_tell_the_kernels_apart(lib):
     for tile, name in ((8, "split_16x16"), (9, "split_32x32")):
         for s in (freg32, tail, point, gather):
             assert icv.plan_name(icv.make_params(s, plan=hooks.tile(tile))).endswith(name)
+    # the hooks reach the kernels that the window kernel replaces where the grid fills the chip, too
+    big = ConvShape("n_big", 22, 21, 21, 256, 128, 3, 3, PT=1, PL=1, PB=1, PR=1)
+    for plan, kernel in ((0, "window"), (hooks.NO_SPLIT, "patch"), (hooks.ANY, "any")):
+        assert hooks.family(icv.plan_name(icv.make_params(big, plan=plan))) == kernel
     for dtype, C in (("bf16", 3), ("u8i8", 1), ("f32", 3)):
         s = ConvShape("n_lowc", 1, 224, 224, C, 64, 7, 7, SY=2, SX=2, PT=3, PL=3, PB=3, PR=3, dtype=dtype)
         assert hooks.family(icv.plan_name(icv.make_params(s))) == "lowc"
@@ -251,7 +255,9 @@ def test_batch_independent_layout_serves_the_tile_of_every_batch_size(lib, C, K)
         layouts.add((L.tile_rows, L.tiles, icv.indirection_bytes(p), icv.packed_filter_bytes(p), icv.zero_row_bytes(p)))
     assert len(layouts) == 1
     assert any(hooks.family(n) == "split" or "_window_32x32_r8_" in n for n in names), names
-    assert any(n.endswith("any_128x32" if K <= 32 else ("any_128x128", "any_128x64")) for n in names), names
+    own = {icv.plan_name(icv.make_params(s.with_(N=n), plan=icv.PLAN_PER_IMAGE | hooks.ANY)) for n in (1, 2, 9, 40, 200)}
+    assert own <= {"mfma_bf16_any_" + t for t in ("128x128", "128x64", "64x64", "128x32")}
+    assert any(n.endswith("any_128x32" if K <= 32 else ("any_128x128", "any_128x64")) for n in own), own
 
 
 def _exact_span(shape, rows):
