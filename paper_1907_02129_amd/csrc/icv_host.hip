@@ -46,8 +46,8 @@ int64_t tile_span_bound(const icv_conv_params* p, int64_t Hout, int64_t Wout, in
     const int64_t arw = rw < 0 ? -rw : rw, aiw = iw < 0 ? -iw : iw;
     int64_t nrw = 0, niw = 0;
     if (rows >= 2) {
-        nrw = (rows - 2) / Wout + 1;
-        niw = (rows - 2) / (Hout * Wout) + 1;
+        nrw = rows - 2 < Wout ? 1 : (rows - 2) / Wout + 1;      // (mostly one: spares a call's host time the divisions)
+        niw = rows - 2 < Hout * Wout ? 1 : (rows - 2) / (Hout * Wout) + 1;
         if (nrw > rows - 1) nrw = rows - 1;
         if (niw > rows - 1) niw = rows - 1;
     }
@@ -327,12 +327,17 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     // of more than three pieces and not in fp32, from the any-channel-count kernel (1.13; 16 of 898 slower by more than 5 %), and from the
     // filter-in-registers kernel in uint8 (1.04).  A batch-independent layout must not depend on N: the pixel-range kernel's
     // problems are compared at eight rounds of tiles there.
-    int window_known = -1;      // (looked for only where it is asked: a call's host time)
+    WindowTimes window_time_of;      // (filled where the first is asked for: a call's host time)
+    bool window_known = false;
+    auto choose_window = [&](int64_t block_rows, double* us) {
+        if (!window_known) window_times(p, *g, &window_time_of);
+        window_known = true;
+        return fastest_window(window_time_of, block_rows, us);
+    };
     auto window_ok = [&]() {
-        if (window_known < 0)
-            window_known = plan_kernel == 0 && plan_staging == 0 && row_bytes >= 16 && (T >= 4 || (lowc_ok && p->dtype == ICV_U8I8)) &&
-                           (window_hook || (hook_tile == 0 && window_fits(p, *g)));
-        return window_known == 1;
+        double us;
+        return plan_kernel == 0 && plan_staging == 0 && row_bytes >= 16 && (T >= 4 || (lowc_ok && p->dtype == ICV_U8I8)) &&
+               (window_hook || (hook_tile == 0 && choose_window(128, &us) >= 0));
     };
     bool window_plan = false;
     if (any_hook && plan_staging == 0 && T * row_bytes < (1ll << 31)) {
@@ -425,8 +430,10 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     if (plan_per_image && staged_rows()) {
         icv_conv_params large = *p;
         large.N = (int32_t)(8 * kCus * 128 * 128 / (Hout * Wout * p->K) + 1);
+        WindowTimes times;
+        window_times(&large, *g, &times);
         double us = 0.0;
-        if (window_hook || (choose_window(&large, *g, 128, &us) >= 0 && us < own_kernel_time(&large, *g))) { to_any_channels(); window_plan = true; }
+        if (window_hook || (fastest_window(times, 128, &us) >= 0 && us < own_kernel_time(&large, *g))) { to_any_channels(); window_plan = true; }
     }
     if (plan_per_image && gathered_rows()) to_any_channels();      // first: the split kernel reads that plan's buffers for any N
     // Too little work to fill the chip: the split-reduction kernel.  It reads the buffers of the filter-in-registers and
@@ -444,7 +451,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         // kernel.  With fewer 16 x 16 tiles than a third of the compute units the latter's smaller tile was level or faster.
         const int64_t tiles16 = (plan_per_image ? p->N * ((Hout * Wout + 15) / 16) : (M + 15) / 16) * ((p->K + 15) / 16);
         if (g->split_tile >= 0 && !split_hook && g->kind != PLAN_MFMA_FREG && 3 * tiles16 > kCus && window_ok()) {
-            const int tile = choose_window(p, *g, g->kind == PLAN_MFMA_ANY ? g->MR : 64, &window_us);
+            const int tile = choose_window(g->kind == PLAN_MFMA_ANY ? g->MR : 64, &window_us);
             if (tile >= 0 && window_us < 0.85 * split_us) {
                 window_plan = tile != kWindowTile32;      // (then it runs whatever the plan's own kernel would take)
                 g->split_tile = window_plan ? -1 : 1;
@@ -479,14 +486,14 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         if (g->split_tile >= 0) g->name = kSplitNames[p->dtype][g->gemm_on_input][g->split_tile];
     }
     if (g->split_tile < 0 && !plan_per_image && staged_rows() &&
-        (window_hook || window_plan || (choose_window(p, *g, 64, &window_time) >= 0 && window_time < 0.85 * own_kernel_time(p, *g)))) {
+        (window_hook || window_plan || (choose_window(64, &window_time) >= 0 && window_time < 0.85 * own_kernel_time(p, *g)))) {
         to_any_channels();
         window_plan = true;
     }
     if (gathered_rows()) to_any_channels();
     g->win_tile = -1;
     if (window_hook && window_ok() && (g->kind == PLAN_MFMA_ANY || g->kind == PLAN_MFMA_FREG)) {
-        g->win_tile = plan_ring ? plan_ring - 2 : choose_window(p, *g, 128, &window_time);
+        g->win_tile = plan_ring ? plan_ring - 2 : choose_window(128, &window_time);
         if (!window_tile_fits(p, *g, g->win_tile, true)) return ICV_ERR_UNSUPPORTED;
     } else if (g->split_tile == 1 && !split_hook && T >= 4 && !g->gemm_on_input && window_tile_fits(p, *g, kWindowTile32, false)) {
         // the 32 x 32 tile with its rows in LDS.  (Always where the filter is in registers: its ring, a power of two of pixel rows
@@ -494,7 +501,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         g->win_tile = kWindowTile32;
     } else if (g->split_tile < 0 && (g->kind == PLAN_MFMA_ANY || (g->kind == PLAN_MFMA_FREG && p->dtype == ICV_U8I8)) &&
                (window_plan || !(g->kind == PLAN_MFMA_ANY && (f32 || row_bytes <= 48))) && window_ok()) {
-        g->win_tile = choose_window(p, *g, g->kind == PLAN_MFMA_ANY ? g->MR : 128, &window_time);
+        g->win_tile = choose_window(g->kind == PLAN_MFMA_ANY ? g->MR : 128, &window_time);
         if (!window_plan && window_time >= 0.85 * own_kernel_time(p, *g)) g->win_tile = -1;
     }
     if (g->win_tile >= 0) g->name = kWindowNames[p->dtype][g->win_tile][g->kind == PLAN_MFMA_ANY ? g->run_variant : 5];

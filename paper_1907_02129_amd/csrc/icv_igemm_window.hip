@@ -75,7 +75,8 @@ static const int64_t kCus = 256;      // (not the device's: a plan must not depe
 static int64_t tiles_of(const icv_conv_params* p, const Geometry& g, const WindowTile& t)
 {
     const int64_t images = g.per_image ? p->N : 1, img_rows = g.per_image ? (int64_t)g.Hout * g.Wout : g.M;
-    return images * ((img_rows + t.MR - 1) / t.MR) * ((p->K + t.NR - 1) / t.NR);
+    // (both are powers of two: a division of 64 bits is some 30 cycles, twelve of them for the six tiles)
+    return images * ((img_rows + t.MR - 1) >> __builtin_ctz((unsigned)t.MR)) * ((p->K + t.NR - 1) >> __builtin_ctz((unsigned)t.NR));
 }
 
 static size_t window_lds_bytes(const WindowTile& t, int T, int64_t cap_rows, int chunk)
@@ -118,37 +119,49 @@ static int window_chunk(const WindowTile& t, int T, int P, int64_t cap_rows, int
     return 0;
 }
 
-static double window_time(const icv_conv_params* p, const Geometry& g, int tile, int64_t cap_rows)
+// Whether window_chunk finds any number of pieces for it: the whole row or, cut, the fewest (LDS use grows with them)
+static bool window_fits_lds(const WindowTile& t, int T, int P, int64_t cap_rows)
 {
-    const WindowTile& t = kWindowTiles[tile];
-    const float* k = kWindowTime[p->dtype][tile];
-    const int P = (p->C * g.elem_bytes + 15) / 16;
-    const double steps = (double)((g.T * P + 1) / 2) / t.WS, kb = (double)cap_rows * P / 64.0;
-    const double tiles = (double)tiles_of(p, g, t), more = tiles > kCus ? tiles / kCus - 1.0 : 0.0;
-    double us = k[0] + k[1] * steps + k[2] * kb + more * (k[3] + k[4] * steps + k[5] * kb);
-    if (P % 2) us += steps * (k[6] + more * k[7]);
-    return us;
+    auto fits = [&](int c) { return window_lds_bytes(t, T, cap_rows, c) <= kLdsPerCu && (cap_rows + 1) * (c | 1) < 65536; };
+    return cap_rows < 65536 && (fits(P) || (P % 2 == 0 && P >= 6 && fits(4)));
 }
 
-static bool tile_fits(const icv_conv_params* p, const Geometry& g, int tile, int64_t* cap_rows)
+static bool window_takes(const Geometry& g, int64_t row_bytes)
 {
+    return row_bytes >= 16 && g.T * row_bytes < (1ll << 27);      // (32-bit offsets in a column block of the filter)
+}
+
+void window_times(const icv_conv_params* p, const Geometry& g, WindowTimes* times)
+{
+    for (int tile = 0; tile < kNumWindowTiles; tile++) times->us[tile] = kNoWindow;
     const int64_t row_bytes = (int64_t)p->C * g.elem_bytes;
-    if (row_bytes < 16 || g.T * row_bytes >= (1ll << 27)) return false;      // (32-bit offsets in a column block of the filter)
-    *cap_rows = tile_span_bound(p, g.Hout, g.Wout, kWindowTiles[tile].MR);
-    return *cap_rows < 65536 && window_chunk(kWindowTiles[tile], g.T, (int)((row_bytes + 15) / 16), *cap_rows, tiles_of(p, g, kWindowTiles[tile])) > 0;
+    if (!window_takes(g, row_bytes)) return;
+    const int P = (int)((row_bytes + 15) / 16);
+    const double all_steps = (double)((g.T * P + 1) / 2);
+    for (int64_t rows = 32; rows <= 128; rows *= 2) {
+        const int64_t cap_rows = tile_span_bound(p, g.Hout, g.Wout, rows);
+        if (cap_rows * P > kWindowPieces) return;      // (nor those of more rows)
+        const double kb = (double)cap_rows * P / 64.0;
+        for (int tile = 0; tile < kNumWindowTiles; tile++) {
+            const WindowTile& t = kWindowTiles[tile];
+            if (t.MR != rows || (t.NR > 32 && 2 * p->K <= t.NR) || !window_fits_lds(t, g.T, P, cap_rows)) continue;
+            const float* k = kWindowTime[p->dtype][tile];
+            const double steps = all_steps / t.WS, tiles = (double)tiles_of(p, g, t), more = tiles > kCus ? tiles / kCus - 1.0 : 0.0;
+            double us = k[0] + k[1] * steps + k[2] * kb + more * (k[3] + k[4] * steps + k[5] * kb);
+            if (P % 2) us += steps * (k[6] + more * k[7]);
+            times->us[tile] = us;
+        }
+    }
 }
 
-int choose_window(const icv_conv_params* p, const Geometry& g, int64_t block_rows, double* us)
+int fastest_window(const WindowTimes& times, int64_t block_rows, double* us)
 {
     int best = -1;
-    for (int tile = 0; tile < kNumWindowTiles; tile++) {
-        const WindowTile& t = kWindowTiles[tile];
-        int64_t cap_rows;
-        if (t.MR > block_rows || (t.NR > 32 && 2 * p->K <= t.NR) || !tile_fits(p, g, tile, &cap_rows)) continue;
-        if (cap_rows * ((p->C * g.elem_bytes + 15) / 16) > kWindowPieces) continue;
-        const double time = window_time(p, g, tile, cap_rows);
-        if (best < 0 || time < *us) { best = tile; *us = time; }
-    }
+    for (int tile = 0; tile < kNumWindowTiles; tile++)
+        if (kWindowTiles[tile].MR <= block_rows && times.us[tile] < kNoWindow && (best < 0 || times.us[tile] < *us)) {
+            best = tile;
+            *us = times.us[tile];
+        }
     return best;
 }
 
@@ -184,17 +197,12 @@ double own_kernel_time(const icv_conv_params* p, const Geometry& g)
     return k[0] + k[1] * stages + k[2] * kb + more * (k[3] + k[4] * stages + k[5] * kb);
 }
 
-bool window_fits(const icv_conv_params* p, const Geometry& g)
-{
-    double us;
-    return choose_window(p, g, 128, &us) >= 0;
-}
-
 bool window_tile_fits(const icv_conv_params* p, const Geometry& g, int tile, bool any_size)
 {
-    int64_t cap_rows;
-    return tile >= 0 && tile < kNumWindowTiles && tile_fits(p, g, tile, &cap_rows) &&
-           (any_size || cap_rows * ((p->C * g.elem_bytes + 15) / 16) <= kWindowPieces);
+    const int64_t row_bytes = (int64_t)p->C * g.elem_bytes, P = (row_bytes + 15) / 16;
+    if (tile < 0 || tile >= kNumWindowTiles || !window_takes(g, row_bytes)) return false;
+    const int64_t cap_rows = tile_span_bound(p, g.Hout, g.Wout, kWindowTiles[tile].MR);
+    return window_fits_lds(kWindowTiles[tile], g.T, (int)P, cap_rows) && (any_size || cap_rows * P <= kWindowPieces);
 }
 
 int launch_igemm_window(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed, const int32_t* ind, void* out,

@@ -185,11 +185,16 @@ int launch_igemm_window_split(const icv_conv_params* p, const Geometry& g, const
 int choose_split(const icv_conv_params* p, const Geometry& g, double* us);      // us: its time, modelled
 int launch_igemm_split(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed,
                        const int32_t* ind, const void* zero_row, void* out, int a_mode, hipStream_t s);
-// the window kernel: its fastest tile of no more than `block_rows` rows (a tile's entries come from one block of them; block form: 128),
-// with its modelled time, -1 if none fits; whether any does; whether this tile fits (any_size: also where it does not pay)
+// the window kernel: the modelled time of every tile (looked for once in a call: a call's host time), kNoWindow where the problem's window
+// does not fit or does not pay; the fastest of no more than `block_rows` rows (a tile's entries come from one block of them; block form:
+// 128) with its time, -1 if there is none; whether this tile fits (any_size: also where it does not pay)
 constexpr int kNumWindowTiles = 6, kWindowTile32 = 3;
-int choose_window(const icv_conv_params* p, const Geometry& g, int64_t block_rows, double* us);
-bool window_fits(const icv_conv_params* p, const Geometry& g);
+constexpr double kNoWindow = 1e30;
+struct WindowTimes {
+    double us[kNumWindowTiles];
+};
+void window_times(const icv_conv_params* p, const Geometry& g, WindowTimes* times);
+int fastest_window(const WindowTimes& times, int64_t block_rows, double* us);
 double own_kernel_time(const icv_conv_params* p, const Geometry& g);      // of the kernel the window kernel would stand in for
 bool window_tile_fits(const icv_conv_params* p, const Geometry& g, int tile, bool any_size);
 int launch_igemm_window(const icv_conv_params* p, const Geometry& g, const void* input, const void* packed, const int32_t* ind, void* out,
