@@ -60,18 +60,18 @@ def test_window_matches_oracle(s, tile, per_image):
 
 
 @pytest.mark.parametrize("s,pieces", [
-    # the window of whole rows does not fit: chunks of equal and of two sizes, in stages and step by step
-    (ConvShape("chunks_even", 1, 30, 60, 512, 40, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=1030), 64),
+    # the window of whole rows does not fit, whatever the tile: chunks of equal and of two sizes, in stages and step by step
+    (ConvShape("chunks_even", 1, 30, 66, 512, 40, 3, 3, PT=1, PL=1, PB=1, PR=1, seed=1030), 64),
     (ConvShape("chunks_uneven", 1, 25, 70, 352, 33, 3, 3, SY=2, SX=2, PT=1, PL=1, PB=1, PR=1, seed=1031), 44),
-    (ConvShape("chunks_of_odd_steps", 1, 12, 140, 416, 40, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="u8i8", zero_point=9, seed=1032), 26),
+    (ConvShape("chunks_of_odd_steps", 1, 12, 180, 416, 40, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="u8i8", zero_point=9, seed=1032), 26),
 ], ids=lambda v: getattr(v, "name", ""))
 @pytest.mark.parametrize("tile", range(len(TILES)), ids=TILES)
 def test_rows_in_chunks(s, pieces, tile):
     p = icv.make_params(s, plan=window(tile))
-    if icv.plan_name(p) == "":
-        pytest.skip("the tile's window does not fit")
-    rows = {"128": 128, "64x": 64, "32x": 32}[TILES[tile][:3]]
-    assert icv.tile_span_bound(p, rows) * (pieces + 1) * 16 > 160 * 1024 or rows < 128
+    assert f"_window_{TILES[tile]}_" in icv.plan_name(p)
+    # window and zero row, rows an odd number of pieces apart, and the entries
+    rows = int(TILES[tile].split("x")[0])
+    assert (icv.tile_span_bound(p, rows) + 1) * (pieces | 1) * 16 + s.R * s.S * rows * 2 > 160 * 1024
     x, w = make_tensors(s)
     buf, _ = run_indirect(s, x, w, plan=window(tile))
     check_against_oracle(s, buf.output.cpu().numpy(), x, w)
