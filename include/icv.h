@@ -103,7 +103,8 @@ ICV_API int icv_output_size(const icv_conv_params* p, int32_t* Hout, int32_t* Wo
  *                 pixels, whatever N is).  Entries are int32 byte offsets, or -- for the kernels that keep a
  *                 tile's input pixels in LDS, and the kernel for very short pixel rows -- a 16-byte record per
  *                 row tile followed by uint16 pixel numbers counted from the tile's base; only the form the plan's
- *                 kernel reads is built.  icv_get_indirection_layout describes it.
+ *                 kernel reads is built (int32 offsets for a batch-independent buffer that the window kernel shares
+ *                 with others).  icv_get_indirection_layout describes it.
  *  packed filter: the [K][R][S][C] filter re-laid as the tiles the GEMM kernel reads, K padded to the tile; for
  *                 ICV_U8I8 on the tensor cores followed by K int32 filter sums (the zero-point term, below)
  *  zero row     : C elements (section 2.3's explicit zero vector), rounded up to 16 bytes

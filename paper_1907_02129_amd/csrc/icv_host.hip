@@ -505,6 +505,14 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         if (!window_plan && window_time >= 0.85 * own_kernel_time(p, *g)) g->win_tile = -1;
     }
     if (g->win_tile >= 0) g->name = kWindowNames[p->dtype][g->win_tile][g->kind == PLAN_MFMA_ANY ? g->run_variant : 5];
+    // A whole batch's buffer is read by the one kernel chosen for it: the window kernel's holds 16-bit entries in block form, half the
+    // bytes.  (A batch-independent one is also read by the kernels that other batch sizes run, which know int32 entries.)
+    g->block_entries = g->kind == PLAN_MFMA_FREG ? 1 : 0;
+    if (g->win_tile >= 0 && g->kind == PLAN_MFMA_ANY && !plan_per_image) {
+        g->block_entries = 1;
+        g->MR = 32;
+        g->zero_row_number = 0xFFFFu;
+    }
     g->img_rows = g->per_image ? Hout * Wout : M;
     g->img_tiles = (g->img_rows + g->MR - 1) / g->MR;
     g->image_bytes = g->per_image ? (int64_t)p->Hin * p->Win * stride_bytes : 0;
@@ -579,9 +587,9 @@ size_t icv_indirection_bytes(const icv_conv_params* p)
     Geometry g;
     if (make_geometry(p, &g) != ICV_OK) return 0;
     const size_t n = (size_t)g.img_tiles * g.MR * g.T;
-    // compact forms (block form of the filter-in-registers plan, range form of the pixel-range plans): a 16-byte
-    // record per block or row tile, then 16-bit entries; else int32 entries
-    if (g.kind == PLAN_MFMA_FREG || g.patch_rows) return (size_t)g.img_tiles * 16 + n * sizeof(uint16_t);
+    // compact forms (block form of the filter-in-registers and whole-batch window plans, range form of the pixel-range plans): a
+    // 16-byte record per block or row tile, then 16-bit entries; else int32 entries
+    if (g.block_entries || g.patch_rows) return (size_t)g.img_tiles * 16 + n * sizeof(uint16_t);
     return n * sizeof(int32_t);
 }
 
@@ -623,7 +631,7 @@ int icv_get_indirection_layout(const icv_conv_params* p, icv_indirection_layout*
     if (!L) return ICV_ERR_INVALID_ARG;
     L->tile_rows = g.MR;
     L->tiles = g.img_tiles;
-    if (g.kind == PLAN_MFMA_FREG) {
+    if (g.block_entries) {
         L->entry_bytes = 2; L->zero_code = 0xFFFF; L->record_bytes = 16;
         L->records_at = 0; L->entries_at = g.img_tiles * 16; L->int32_entries_at = -1;
     } else if (g.patch_rows) {

@@ -210,18 +210,17 @@ int launch_igemm_window(const icv_conv_params* p, const Geometry& g, const void*
 {
     if (g.win_tile < 0 || g.win_tile >= kNumWindowTiles) return ICV_ERR_UNSUPPORTED;
     const WindowTile& t = kWindowTiles[g.win_tile];
-    const bool blocks32 = g.kind == PLAN_MFMA_FREG;      // entries in block form
     WindowArgs a{};      // every field starts at zero; the ones this call uses are set below
     a.a = (const uint8_t*)input;
     a.w = (const uint8_t*)packed;
     a.out = out;
-    if (blocks32) a.ent = (const uint16_t*)((const int4*)ind + g.img_tiles);
+    if (g.block_entries) a.ent = (const uint16_t*)((const int4*)ind + g.img_tiles);
     else a.ind = ind;
     a.row_bytes = p->C * g.elem_bytes;
     a.stride_bytes = g.in_stride * g.elem_bytes;
     a.image_bytes = g.image_bytes;
     while ((1 << a.block_shift) < g.MR) ++a.block_shift;
-    if (a.row_bytes < 16 || (1 << a.block_shift) != g.MR || (blocks32 ? g.MR != 32 : g.MR % t.MR != 0)) return ICV_ERR_UNSUPPORTED;
+    if (a.row_bytes < 16 || (1 << a.block_shift) != g.MR || (g.block_entries ? g.MR != 32 : g.MR % t.MR != 0)) return ICV_ERR_UNSUPPORTED;
     const int64_t images = g.per_image ? p->N : 1, img_tiles = (g.img_rows + t.MR - 1) / t.MR, n_tiles = (p->K + t.NR - 1) / t.NR;
     const int64_t tiles = images * img_tiles * n_tiles;
     if (tiles >= (1ll << 31) - 8 || g.img_tiles >= (1ll << 31)) return ICV_ERR_UNSUPPORTED;

@@ -104,6 +104,7 @@ struct Geometry {
     int32_t run_variant;
     int32_t split_tile;      // >= 0: tile of the split-reduction kernel, which then runs instead of the plan's own (same buffers)
     int32_t win_tile;        // >= 0: tile of the window kernel, which then runs instead of the any-channel-count or split-reduction one
+    int32_t block_entries;   // 1: 16-bit entries in block form, MR = 32 (filter in registers; the window kernel on a whole batch)
     const char* name;
     EpilogueArgs ep;         // output stage of this call (plain: no bias, no ReLU, accumulator type)
     bool ep_plain;

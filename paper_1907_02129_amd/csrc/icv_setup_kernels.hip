@@ -313,7 +313,7 @@ __global__ __launch_bounds__(256) void k_build_indirection(IndArgs a)
     }
 }
 
-// Block form (filter-in-registers plan): per block of 32 consecutive output pixels one 16-byte record {base byte
+// Block form (filter-in-registers plan, window kernel on a whole batch): per block of 32 consecutive output pixels one 16-byte record {base byte
 // offset, 0, base pixel, 0} -- the base is the closed-form lower bound of icv_pixel_range.h for the block's first
 // pixel, so a kernel can compute it without reading anything -- and per (kernel element, row) the entry as a 16-bit
 // pixel number counted from that base, 0xFFFF for the zero row (and for rows past M).  Physical order
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(256) void k_build_block_indirection(BlockIndArgs a)
 
 int launch_build_indirection(const icv_conv_params* p, const Geometry& g, int32_t* ind, hipStream_t s)
 {
-    if (g.kind == PLAN_MFMA_FREG) {
+    if (g.block_entries) {
         BlockIndArgs b{};
         b.rec = (int4*)ind;
         b.ent = (uint16_t*)(b.rec + g.img_tiles);

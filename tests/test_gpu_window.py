@@ -48,6 +48,8 @@ def test_window_matches_oracle(s, tile, per_image):
     name = icv.plan_name(icv.make_params(s, plan=plan))
     print("conv", s.name, name, flush=True)
     assert f"_window_{TILES[tile]}_" in name
+    # block-form entries, or int32 ones where other kernels read the buffer too
+    assert icv.get_indirection_layout(icv.make_params(s, plan=plan)).entry_bytes == (4 if per_image and "_any_" in name else 2)
     x, w = make_tensors(s)
     buf, xd = run_indirect(s, x, w, plan=plan)
     check_against_oracle(s, buf.output.cpu().numpy(), x, w)

@@ -400,6 +400,30 @@ def test_range_records_are_counted_in_the_buffer_size(lib):
     assert _status(lib, CONFIGS["cfg5a_1x1"], plan=icv.PLAN_WINDOW) == icv.ICV_ERR_UNSUPPORTED
 
 
+@pytest.mark.parametrize("own,s", [
+    ("lowc", ConvShape("short_rows", 4, 40, 39, 16, 48, 3, 3, PT=1, PL=1, PB=1, PR=1)),
+    ("lowc", ConvShape("short_rows_u8", 1, 9, 9, 32, 8, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype="u8i8")),
+    ("patch", ConvShape("pixel_range", 24, 28, 28, 256, 128, 3, 3, PT=1, PL=1, PB=1, PR=1)),
+    ("any", ConvShape("gathered", 32, 27, 27, 48, 192, 3, 3, PT=1, PL=1, PB=1, PR=1)),
+    ("gather", ConvShape("gathered_aligned", 24, 40, 40, 96, 64, 3, 3, PT=1, PL=1, PB=1, PR=1)),
+], ids=lambda v: getattr(v, "name", v))
+def test_window_kernel_reads_16_bit_entries(own, s):
+    """A whole batch's buffer in block form: half the bytes of int32 entries, and those of the 16-bit forms of the kernels it has
+    its problems from, but for a record per 32 output pixels instead of one per 64 or more."""
+    p, q = icv.make_params(s), icv.make_params(s, plan=hooks.NO_SPLIT)
+    assert hooks.family(icv.plan_name(p)) == "window" and hooks.family(icv.plan_name(q)) == own
+    Hout, Wout = icv.output_size(p)
+    blocks, T = -(-s.N * Hout * Wout // 32), s.R * s.S
+    L = icv.get_indirection_layout(p)
+    assert (L.tile_rows, L.tiles, L.entry_bytes, L.zero_code) == (32, blocks, 2, 0xFFFF)
+    assert icv.indirection_bytes(p) == blocks * (16 + 64 * T)
+    if own in ("lowc", "patch"):
+        assert icv.indirection_bytes(p) <= icv.indirection_bytes(q) + blocks * 16      # (the records alone)
+    # the batch-independent buffer is also read by kernels that know int32 entries
+    one = icv.make_params(s, plan=icv.PLAN_PER_IMAGE)
+    assert icv.get_indirection_layout(one).entry_bytes == (4 if hooks.family(icv.plan_name(one)) == "window" else 2)
+
+
 def test_batch_independent_indirection_buffer_sizes(lib):
     """ICV_PLAN_PER_IMAGE: the buffer describes one image, so its size does not depend on N (section 2.3 re-initialises
     the buffer when the batch grows; with one image per buffer there is nothing to re-initialise)."""
