@@ -321,9 +321,9 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         g->name = kAnyNames[p->dtype][g->run_variant];
     };
     // The window kernel takes a problem from another where its modelled time is 0.85 of the other's -- the models are off by 10 % -- :
-    // rows of 16 and 32 bytes from the short-row kernel (always: of 577 drawn problems four were slower, by up to 10 %; on average 1.13
-    // times as fast in bfloat16, 1.45 in uint8; fewer than four kernel elements in uint8 alone, 1.38 on 97 1x1 problems against 1.06
-    // with 8 of 35 slower in bfloat16), from the pixel-range kernel (1.36 in bfloat16, 1.39 in uint8, 2.0 in fp32) and, with rows
+    // rows of 16 and 32 bytes from the short-row kernel (420 drawn 3x3 and 5x5 problems took 0.87 of its time in bfloat16, 0.68 in uint8;
+    // fewer than four kernel elements in uint8 alone, 1.38 times as fast on 97 1x1 problems against 1.06
+    // with 8 of 35 slower in bfloat16) except where short_stays says so, from the pixel-range kernel (1.36 in bfloat16, 1.39 in uint8, 2.0 in fp32) and, with rows
     // of more than three pieces and not in fp32, from the any-channel-count kernel (1.13; 16 of 898 slower by more than 5 %), and from the
     // filter-in-registers kernel in uint8 (1.04).  A batch-independent layout must not depend on N: the pixel-range kernel's
     // problems are compared at eight rounds of tiles there.
@@ -339,6 +339,10 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         return plan_kernel == 0 && plan_staging == 0 && row_bytes >= 16 && (T >= 4 || (lowc_ok && p->dtype == ICV_U8I8)) &&
                (window_hook || (hook_tile == 0 && choose_window(128, &us) >= 0));
     };
+    // bfloat16, 17 to 32 columns, up to two tiles of the short-row kernel on a compute unit: 24 of 35 drawn problems were 5 to 12 % slower on
+    // the window kernel (1.06 on average, 4.2 against 4.6 us); with more tiles 33 took 0.76 of the time, with up to 16 columns 30 took 0.96,
+    // with 33 to 64 22 took 0.97.  (Not where the layout must not depend on N.)
+    const bool short_stays = p->dtype == ICV_BF16 && !plan_per_image && !window_hook && p->K > 16 && p->K <= 32 && (M + 63) / 64 <= 2 * kCus;
     bool window_plan = false;
     if (any_hook && plan_staging == 0 && T * row_bytes < (1ll << 31)) {
         to_any_channels();
@@ -355,7 +359,7 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         g->n_stages = g->T;
         g->zero_row_number = 0xFFFFu;
         g->name = kFregNames[p->dtype][freg_wn == 4 ? 2 : freg_wn - 1][freg_mb - 1];
-    } else if (lowc_ok && row_bytes >= 16 && !f32 && window_ok()) {
+    } else if (lowc_ok && row_bytes >= 16 && !f32 && !short_stays && window_ok()) {
         to_any_channels();
         window_plan = true;
     } else if (lowc_ok) {

@@ -433,6 +433,15 @@ def test_256x128_tiles_keep_their_problems(n, hw, C, K, k):
     assert icv.plan_name(icv.make_params(s)) == icv.plan_name(icv.make_params(s, plan=hooks.NO_SPLIT)) == "mfma_bf16_256x128_c4x2_patch"
 
 
+@pytest.mark.parametrize("dtype,C,K,n,kernel", [
+    ("bf16", 16, 32, 1, "lowc"), ("bf16", 8, 17, 4, "lowc"), ("bf16", 16, 32, 32, "lowc"), ("bf16", 16, 32, 33, "window"), ("bf16", 16, 16, 1, "window"),
+    ("bf16", 16, 33, 1, "window"), ("u8i8", 32, 32, 1, "window")])
+def test_short_rows_and_few_columns(dtype, C, K, n, kernel):
+    """17 to 32 bfloat16 columns in at most 512 row tiles of 64: the short-row kernel is faster there."""
+    s = ConvShape("short", n, 32, 32, C, K, 3, 3, PT=1, PL=1, PB=1, PR=1, dtype=dtype)
+    assert hooks.family(icv.plan_name(icv.make_params(s))) == kernel
+
+
 def test_batch_independent_indirection_buffer_sizes(lib):
     """ICV_PLAN_PER_IMAGE: the buffer describes one image, so its size does not depend on N (section 2.3 re-initialises
     the buffer when the batch grows; with one image per buffer there is nothing to re-initialise)."""
