@@ -326,7 +326,9 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
     // with 8 of 35 slower in bfloat16) except where short_stays says so, from the pixel-range kernel (1.36 in bfloat16, 1.39 in uint8, 2.0 in fp32) and, with rows
     // of more than three pieces and not in fp32, from the any-channel-count kernel (1.13; 16 of 898 slower by more than 5 %), and from the
     // filter-in-registers kernel in uint8 (1.04).  A batch-independent layout must not depend on N: the pixel-range kernel's
-    // problems are compared at eight rounds of tiles there.
+    // problems are compared at eight rounds of tiles there, and at 1.00, because the other layout also opens small batches to the
+    // split-reduction kernels: 135 drawn problems between 0.85 and 1.00 took 0.50 (bfloat16), 0.58 (uint8) and 0.31 (fp32) of the time at
+    // their batch sizes, five of them 1.06 to 1.19.
     WindowTimes window_time_of;      // (filled where the first is asked for: a call's host time)
     bool window_known = false;
     auto choose_window = [&](int64_t block_rows, double* us) {
