@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import icv_layout as layout
 import plan_hooks as hooks
 from oracle import direct_conv as oracle
 from paper_1907_02129_amd import binding as icv
@@ -52,6 +53,9 @@ def test_window_matches_oracle(s, tile, per_image):
     assert icv.get_indirection_layout(icv.make_params(s, plan=plan)).entry_bytes == (4 if per_image and "_any_" in name else 2)
     x, w = make_tensors(s)
     buf, xd = run_indirect(s, x, w, plan=plan)
+    one = s.with_(N=1) if per_image else s          # what the buffer describes
+    got, tail = layout.logical_indirection(buf.p, buf.indirection, one.N * buf.Hout * buf.Wout)
+    assert np.array_equal(got, oracle.indirection(one)) and np.all(tail == -1)
     check_against_oracle(s, buf.output.cpu().numpy(), x, w)
     if icv.im2col_bytes(buf.p):                     # the patch matrix by the same filter, through the kernel of the plan's buffers
         out2, _ = run_im2col(s, buf, xd)
