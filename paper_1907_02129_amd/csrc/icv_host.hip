@@ -341,10 +341,11 @@ int make_geometry(const icv_conv_params* p, Geometry* g)
         return plan_kernel == 0 && plan_staging == 0 && row_bytes >= 16 && (T >= 4 || (lowc_ok && p->dtype == ICV_U8I8)) &&
                (window_hook || (hook_tile == 0 && choose_window(128, &us) >= 0));
     };
-    // bfloat16, 17 to 32 columns, up to two tiles of the short-row kernel on a compute unit: 24 of 35 drawn problems were 5 to 12 % slower on
-    // the window kernel (1.06 on average, 4.2 against 4.6 us); with more tiles 33 took 0.76 of the time, with up to 16 columns 30 took 0.96,
-    // with 33 to 64 22 took 0.97.  (Not where the layout must not depend on N.)
-    const bool short_stays = p->dtype == ICV_BF16 && !plan_per_image && !window_hook && p->K > 16 && p->K <= 32 && (M + 63) / 64 <= 2 * kCus;
+    // bfloat16, one whole column block, up to two tiles of the short-row kernel on a compute unit, patches of up to 288 bytes (3x3 on 32-byte
+    // rows): it took 0.93 of the window kernel's time on 87 drawn problems (0.80 to 1.01; 4.2 against 4.6 us).  With 17 to 31 columns 173
+    // were level (0.995), up to 16 columns 30 took 1.04, 33 to 64 22 took 1.03, more tiles 33 took 1.3 and longer patches 90
+    // 1.07 to 1.17 times as long on it.  (Not where the layout must not depend on N.)
+    const bool short_stays = p->dtype == ICV_BF16 && !plan_per_image && !window_hook && p->K == 32 && (M + 63) / 64 <= 2 * kCus && T * row_bytes <= 288;
     bool window_plan = false;
     if (any_hook && plan_staging == 0 && T * row_bytes < (1ll << 31)) {
         to_any_channels();
