@@ -1,6 +1,6 @@
 // Tensor-core Indirect GEMM for very few input channels (first-layer convolutions): pixel rows of 8, 16 or 32 bytes, of one
 // to three bf16, one to four uint8 or one to three fp32 channels.  (Rows of 16 and 32 bytes go to the window kernel where it is
-// built for them; pointwise bfloat16 ones and those whose window does not fit stay.)
+// built for them; pointwise bfloat16 ones, those whose window does not fit, and small bfloat16 layers of 32 columns stay.)
 //
 // With so short rows one kernel element is less than an MFMA k-step, so the two nested loops of Listing 3
 // (kernel elements outside, channels inside) are flattened: the reduction index is k = tap*C + c, the whole
